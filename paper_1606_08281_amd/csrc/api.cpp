@@ -55,6 +55,20 @@ uint32_t lik::compute_units() {
     return (uint32_t)cus;
 }
 
+uint32_t lik::split_waves() { return std::min(compute_units() * kSplitWavesPerCu, 4096u); }
+
+int32_t lik::split_goal(size_t slots, size_t chunks) {
+    if (slots == 0 || chunks >= kSplitChunks) return 0;
+    return (int32_t)std::min<size_t>(split_waves() / slots, 64);
+}
+
+int32_t lik::flow_spare(int64_t intervals, int h_max, int64_t items_max) {
+    const int64_t least = kPropBlock >> kSplitMax;  // particles of the smallest item
+    const int64_t most = intervals * std::min<int64_t>(64, (h_max + least - 1) / least);
+    // an empty wavefront costs its dispatch: bounded
+    return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, 1 << 18));
+}
+
 namespace {
 
 // Kernel timing (lik_timing_enable / lik_timing_read).
@@ -387,7 +401,7 @@ size_t lik_workspace_size(lik_network_t net, int32_t n_theta, int32_t n_traj,
     b += align256(F * 4) * 4;                 // tcur, fstatus, fflags, cost
     b += align256(F);                         // pool
     b += align256(F * 8) * 2;                 // fll, fevents
-    b += align256(F * (Hp / 64) * 4);         // items
+    b += align256(item_list_capacity(F * (Hp / 64)) * 4);  // items
     b += align256(kMaxGroups * 4);            // item_count
     b += align256(kMaxGroups * 4);            // item_cursor
     b += 2 * align256(kMaxGroups * kCostKeys * 4) + align256(2 * 4);  // ordering passes
@@ -575,7 +589,8 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
     // takes the per-interval schedule, with the same results
     const size_t items_max = (size_t)n_theta * (size_t)total * (size_t)nchunk;
     bool flow = net->tuning.schedule == 1 && items_max < ((size_t)1 << 26);
-    EngineLayout L = carve_engine(p, F, F * nchunk, request_state_bytes((int64_t)F, net->U, Hp),
+    EngineLayout L = carve_engine(p, F, item_list_capacity(F * nchunk),
+                                  request_state_bytes((int64_t)F, net->U, Hp),
                                   flow_ring_capacity(F, nchunk));
     L.e.f_lo = 0;
     L.e.f_hi = (int32_t)F;
@@ -613,6 +628,11 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
         G.spec_p = no_alloc ? loaded_specialized_kernel(*net, precision, kSpecPersistent)
                             : specialized_kernel(*net, precision, &err, kSpecPersistent);
 
+    if (!G.persistent) {  // the per-interval schedule's splitting
+        L.e.split_goal = split_goal(F, F * nchunk);
+        G.max_items = (unsigned)(F * (size_t)std::max(nchunk, L.e.split_goal));
+    }
+
     // flow schedule: its kernel and one wavefront per work item the batch can
     // have (every interval of every filter in groups of 64)
     hipFunction_t flow_spec = nullptr;
@@ -633,7 +653,9 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
         flow = per_cu >= kFlowMinWavesPerCu;
     }
     if (flow) {
-        flow_waves = (unsigned)std::max<size_t>(items_max, 1);
+        L.fa.split_waves = split_waves();
+        L.fa.spare = flow_spare((int64_t)n_theta * total, H, (int64_t)items_max);
+        flow_waves = (unsigned)std::max<size_t>(items_max + (size_t)L.fa.spare, 1);
         L.fa.g_par = (int32_t)std::max<size_t>(
             1, F * nchunk / std::max<uint32_t>(L.e.pool_min_items, 1u));
         int dev = 0, khz = 0;

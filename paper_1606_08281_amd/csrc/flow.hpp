@@ -33,9 +33,11 @@
 // appends its items while fewer than `backlog` wait.  Urgent filters always
 // append, and so wait only behind a short ring.  No deadlock: a filter is
 // parked only while items wait, and the last of them to finish un-parks.
-// At most one interval of items per filter is outstanding, so at most
-// sum(groups of 64) <= capacity / 2 entries sit in a ring and a producer
-// never waits for a slot that no wavefront has claimed.  Hand-offs between wavefronts (item results before the
+// At most one interval of items per filter is outstanding: its groups of 64,
+// or when split no more than its share of split_waves.  The share only grows
+// as filters finish, so at most sum(groups of 64) + split_waves <= capacity
+// entries sit in a ring and a producer never waits for a slot that no
+// wavefront has claimed.  Hand-offs between wavefronts (item results before the
 // weighing, the weighing's state before the next items) are agent-scope
 // release/acquire pairs.
 #pragma once
@@ -139,12 +141,37 @@ __device__ __forceinline__ int32_t item_backlog(const FlowArgs &fa) {
                      ctl_load(fa, kCtlHead + 64 * kRingItems));
 }
 
-// Writes the work items of filter f (pool size G, state already released)
+// Writes the work items of filter f (item code `code`, state already released)
 // to the item ring.
-__device__ __forceinline__ void emit_items(const EngineArgs &e, const FlowArgs &fa, int f, int G,
-                                           int lane) {
-    const int n_items = ((e.desc[f].Hp >> 6) + G - 1) / G;  // <= 64: one lane per item
-    ring_put(fa, kRingItems, n_items, ((uint32_t)f << 6) | (uint32_t)(lane * G), lane);
+__device__ __forceinline__ void emit_items(const EngineArgs &e, const FlowArgs &fa, int f,
+                                           int code, int lane) {
+    const int n_items = code_items(code, e.desc[f].H);  // <= 64: one lane per item
+    ring_put(fa, kRingItems, n_items, ((uint32_t)f << 6) | (uint32_t)(lane * code_step(code)),
+             lane);
+}
+
+// Items each filter's interval should be cut into so that the filters not
+// yet finished fill the GPU (0: no splitting).
+__device__ __forceinline__ int split_goal(const FlowArgs &fa, int finished) {
+    return (int)(fa.split_waves / (uint32_t)max(fa.n_slots - finished, 1));
+}
+
+// The launch has one wavefront per group of 64 particles of every interval
+// and fa.spare more; kCtlSpare counts those that no item needs.  A filter
+// whose interval takes fewer items than groups gives the rest; one that is
+// split takes the difference, or is not split when too few are left, so an
+// item always finds a wavefront.  One lane only.
+__device__ __forceinline__ int settle_spare(const FlowArgs &fa, int code, int H, int nchunk) {
+    const int need = code_items(code, H) - nchunk;
+    uint32_t *spare = &fa.ctl[kCtlSpare];
+    if (need < 0)
+        __hip_atomic_fetch_add(spare, (uint32_t)-need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (need <= 0) return code;
+    const int had = (int)__hip_atomic_fetch_sub(spare, (uint32_t)need, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+    if (had >= need) return code;
+    __hip_atomic_fetch_add(spare, (uint32_t)need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return 0;
 }
 
 // While the item ring is short and filters are parked, takes one parked
@@ -172,10 +199,10 @@ __device__ __forceinline__ bool flow_unpark(const EngineArgs &e, const FlowArgs 
     if (f < 0) return false;
     // acquire the parked filter's state; release it again to the items' takers
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const int G = (int)e.pool[f] + 1;
+    const int code = (int)e.pool[f];
     __threadfence();
     __syncthreads();
-    emit_items(e, fa, f, G, lane);
+    emit_items(e, fa, f, code, lane);
     return true;
 }
 
@@ -418,14 +445,20 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
     const int lane = lane_id();
     __syncthreads();  // the weighing's state (tcur, ancestors) from every lane
     // lane 0 wrote tcur: its reading decides, for every lane
-    const int G = __builtin_amdgcn_readfirstlane(pool_size(e, f, cost, fa.g_par));
-    const int nchunk = e.desc[f].Hp >> 6;
-    const int n_items = (nchunk + G - 1) / G;
+    const int H = e.desc[f].H;
+    int code = 0;
+    if (lane == 0)
+        code = settle_spare(fa,
+                            item_code(e, f, cost, fa.g_par,
+                                      split_goal(fa, (int)ctl_load(fa, kCtlFinished))),
+                            H, e.desc[f].Hp >> 6);
+    code = __builtin_amdgcn_readfirstlane(code);
+    const int n_items = code_items(code, H);
     const int park = __builtin_amdgcn_readfirstlane(
-        (int)(!flow_urgent(e, fa, f, cost, G) && item_backlog(fa) >= (int32_t)fa.backlog));
+        (int)(!flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
     if (lane == 0) {
         e.cost[f] = cost;
-        e.pool[f] = (uint8_t)(G - 1);
+        e.pool[f] = (uint8_t)code;
         __hip_atomic_store(&fa.remaining[f], (uint32_t)n_items, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -435,11 +468,11 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
     if (park)
         ring_put(fa, kRingParked, 1, (uint32_t)f, lane);
     else
-        emit_items(e, fa, f, G, lane);
+        emit_items(e, fa, f, code, lane);
 }
 
 // One work item per wavefront (a grid of at least as many wavefronts as the
-// batch has work items; the hardware starts each as a slot frees): claim the
+// batch has work items, settle_spare; the hardware starts each as a slot frees): claim the
 // next ring position, run its item, and if it was its filter's last of the
 // interval, weigh the filter and write its next items.  A wavefront whose
 // position is never filled leaves when every filter is done.  One item per

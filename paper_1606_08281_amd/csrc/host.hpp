@@ -102,6 +102,15 @@ const lik_tuning *autotune_candidates(int *n);
 int fail(int code, const std::string &msg);
 int hip_fail(hipError_t e, const char *where);
 uint32_t compute_units();  // of the current device
+// Wavefronts that batches too small to fill the device are spread over.
+uint32_t split_waves();
+// Items per slot for the per-interval schedule: `slots` slots with `chunks`
+// groups of 64 particles in all (0: no splitting).
+int32_t split_goal(size_t slots, size_t chunks);
+// Wavefronts a flow launch takes beyond one per group of 64 particles, so that
+// every interval can be split: `intervals` filter-intervals of at most h_max
+// particles with items_max groups in all.
+int32_t flow_spare(int64_t intervals, int h_max, int64_t items_max);
 unsigned persistent_waves();  // grid of the persistent propagation kernels
 bool tuning_valid(const lik_tuning &t);
 const char *tuning_rule();

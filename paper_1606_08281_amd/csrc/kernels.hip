@@ -197,6 +197,11 @@ __device__ __forceinline__ int order_gpar(const EngineArgs &e) {
     return (int)max(1u, e.pool_chunks / max(e.pool_min_items, 1u));
 }
 
+// Key of a slot's items: c expected events of the slot, H particles.
+__device__ __forceinline__ int item_key(uint32_t c, int H, int code) {
+    return duration_key((uint64_t)(c / (uint32_t)H) * (uint64_t)(code < kSplitCode ? code + 1 : 1));
+}
+
 __global__ __launch_bounds__(kOrderBlock) void k_order_count(EngineArgs e) {
     __shared__ uint32_t hist[kMaxGroups * kCostKeys];
     __shared__ uint32_t max_per;
@@ -206,10 +211,10 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_count(EngineArgs e) {
     const int f = e.f_lo + (int)(blockIdx.x * kOrderBlock + threadIdx.x);
     if (f < e.f_hi && slot_active(e, f)) {
         const uint32_t c = e.cost[f];
-        const int nchunk = e.desc[f].Hp >> 6;
-        const int g = pool_size(e, f, c, order_gpar(e));
-        const int key = duration_key((uint64_t)(c / (uint32_t)e.desc[f].H) * (uint64_t)g);
-        atomicAdd(&hist[e.desc[f].group * kCostKeys + key], (uint32_t)((nchunk + g - 1) / g));
+        const int code = item_code(e, f, c, order_gpar(e), e.split_goal);
+        const int key = item_key(c, e.desc[f].H, code);
+        atomicAdd(&hist[e.desc[f].group * kCostKeys + key],
+                  (uint32_t)code_items(code, e.desc[f].H));
         atomicMax(&max_per, c / (uint32_t)e.desc[f].H);
     }
     __syncthreads();
@@ -254,14 +259,12 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
     const int f = e.f_lo + (int)(blockIdx.x * kOrderBlock + threadIdx.x);
     const bool on = f < e.f_hi && slot_active(e, f);
     uint32_t c = 0, n_items = 0, local = 0;
-    int g = 1, gk = 0;
+    int code = 0, gk = 0;
     if (on) {
         c = e.cost[f];
-        const int nchunk = e.desc[f].Hp >> 6;
-        g = pool_size(e, f, c, order_gpar(e));  // as in the counting pass
-        const int key = duration_key((uint64_t)(c / (uint32_t)e.desc[f].H) * (uint64_t)g);
-        gk = e.desc[f].group * kCostKeys + key;
-        n_items = (uint32_t)((nchunk + g - 1) / g);
+        code = item_code(e, f, c, order_gpar(e), e.split_goal);  // as in the counting pass
+        gk = e.desc[f].group * kCostKeys + item_key(c, e.desc[f].H, code);
+        n_items = (uint32_t)code_items(code, e.desc[f].H);
         local = atomicAdd(&lcount[gk], n_items);
     }
     __syncthreads();
@@ -270,7 +273,8 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
     __syncthreads();
     if (!on) return;
     const uint32_t pos = lcount[gk] + local;
-    for (uint32_t q = 0; q < n_items; ++q) e.items[pos + q] = ((uint32_t)f << 6) | (q * g);
+    for (uint32_t q = 0; q < n_items; ++q)
+        e.items[pos + q] = ((uint32_t)f << 6) | (q * (uint32_t)code_step(code));
     // Wavefront priority: the slots whose particles are expected to need
     // the most events are the ones the iteration waits for; their
     // wavefronts issue first on a SIMD they share with lighter ones.
@@ -279,7 +283,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
     int prio = 0;
     if (e.priority && per > 0)
         prio = (uint64_t)per * 4u >= max_per ? 3 : (uint64_t)per * 32u >= max_per ? 1 : 0;
-    e.pool[f] = (uint8_t)((prio << 6) | (g - 1));
+    e.pool[f] = (uint8_t)((prio << 6) | code);
 }
 
 __global__ void k_order_reset(EngineArgs e) {
@@ -314,7 +318,11 @@ __global__ void k_flow_init(FlowArgs fa) {
         fa.ring[i] = (uint64_t)(i & fa.mask) << 32;  // free for position i
     if (blockIdx.x == 0) {
         for (int w = threadIdx.x; w < kCtlArgs; w += blockDim.x) fa.ctl[w] = 0u;
-        if (threadIdx.x == 0) *const_cast<FlowArgs *>(flow_args_copy(fa.ctl)) = fa;
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            *const_cast<FlowArgs *>(flow_args_copy(fa.ctl)) = fa;
+            fa.ctl[kCtlSpare] = (uint32_t)fa.spare;
+        }
     }
 }
 
@@ -328,11 +336,12 @@ __global__ void k_flow_seed(EngineArgs e, FlowArgs fa, int pass) {
         if (pass == 0) atomicAdd(&fa.ctl[kCtlFinished], 1u);
         return;
     }
-    const int G = pool_size(e, f, e.cost[f], fa.g_par);
-    const bool urgent = flow_urgent(e, fa, f, e.cost[f], G);
+    int code = item_code(e, f, e.cost[f], fa.g_par, split_goal(fa, 0));
+    const bool urgent = flow_urgent(e, fa, f, e.cost[f], code < kSplitCode ? code + 1 : 1);
     if (urgent != (pass == 0)) return;
-    const int n_items = ((e.desc[f].Hp >> 6) + G - 1) / G;
-    e.pool[f] = (uint8_t)(G - 1);
+    code = settle_spare(fa, code, e.desc[f].H, e.desc[f].Hp >> 6);
+    const int n_items = code_items(code, e.desc[f].H);
+    e.pool[f] = (uint8_t)code;
     fa.remaining[f] = (uint32_t)n_items;
     const bool park = !urgent && atomicAdd(&fa.ctl[kCtlSeedItems], (uint32_t)n_items) >= fa.backlog;
     const int r = park ? kRingParked : kRingItems;
@@ -341,7 +350,8 @@ __global__ void k_flow_seed(EngineArgs e, FlowArgs fa, int pass) {
     uint64_t *ring = fa.ring + (size_t)r * (fa.mask + 1);
     for (int k = 0; k < n; ++k) {
         const uint32_t pos = base + (uint32_t)k;
-        const uint32_t entry = park ? (uint32_t)f : (((uint32_t)f << 6) | (uint32_t)(k * G));
+        const uint32_t entry =
+            park ? (uint32_t)f : (((uint32_t)f << 6) | (uint32_t)(k * code_step(code)));
         ring[pos & fa.mask] = ((uint64_t)(pos + 1u) << 32) | entry;
     }
 }

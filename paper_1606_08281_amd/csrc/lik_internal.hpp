@@ -32,6 +32,31 @@ __host__ __device__ constexpr int pool_lds_cap(int U) { return kPoolLdsWords / (
 constexpr int kSortPerLane = 6;
 constexpr int kSortBuckets = 64;  // half octaves of the expected cost, below the heaviest
 
+// A slot's item code (low 6 bits of EngineArgs::pool): codes below kSplitCode
+// are G - 1 for items of G * 64 particles (G <= 16: pool_lds_cap of one
+// species); code kSplitCode + s is an item of 64 >> s particles, whose idle
+// lanes draw the running lanes' coming events ahead of time, so a particle's
+// events follow each other sooner.  A slot has at most 64 items.
+constexpr int kSplitCode = 32;
+constexpr int kSplitMax = 4;  // items of 32, 16, 8 or 4 particles
+__host__ __device__ constexpr int code_span(int code) {  // particles per item
+    return code < kSplitCode ? (code + 1) * kPropBlock : kPropBlock >> (code - kSplitCode);
+}
+__host__ __device__ constexpr int code_items(int code, int H) {
+    return (H + code_span(code) - 1) / code_span(code);
+}
+// Step between the chunk numbers (low 6 bits) of a slot's consecutive items,
+// and the particles a chunk number counts.
+__host__ __device__ constexpr int code_step(int code) { return code < kSplitCode ? code + 1 : 1; }
+__host__ __device__ constexpr int code_unit(int code) {
+    return code < kSplitCode ? kPropBlock : code_span(code);
+}
+// Items are split only for particles expected to need this many events: a
+// shorter item is over before its hand-off is.
+constexpr uint32_t kSplitMinEvents = 48;
+// Wavefronts per compute unit that splitting fills the GPU to.
+constexpr uint32_t kSplitWavesPerCu = 12;
+
 // Reaction kinds after validation of the reactant orders.
 enum : int32_t { kOrder0 = 0, kOrder1 = 1, kOrder2Homo = 2, kOrder2Hetero = 3 };
 
@@ -88,7 +113,7 @@ struct EngineArgs {
     uint32_t *fflags;         // [slots]
     uint64_t *fevents;        // [slots] SSA events applied
     uint32_t *cost;           // [slots] expected events of the next interval (ordering key)
-    uint8_t *pool;            // [slots] (wave priority << 6) | (particles per item / 64 - 1)
+    uint8_t *pool;            // [slots] (wave priority << 6) | item code
     uint32_t *items;          // propagation work items (slot << 6 | chunk), grouped
     uint32_t *item_count;     // [kMaxGroups] items written per group
     uint32_t *item_cursor;    // [kMaxGroups] next item to take (persistent kernels)
@@ -110,6 +135,8 @@ struct EngineArgs {
     int32_t priority;         // raise the wave priority of the heaviest slots
     uint32_t pool_min_items;  // work items an iteration keeps before pools grow
     int32_t h_max;            // most particles of any active slot (LDS of k_weigh)
+    int32_t split_goal;       // per-interval schedule: items a slot is cut into, its groups of
+                              // 64 particles allowing (0: only by its pool size)
     uint32_t group_off[kMaxGroups];  // first item of each group
 };
 
@@ -125,6 +152,7 @@ enum : int {
     kCtlAbort = 160,      // nonzero: a wavefront saw no progress for stall_ticks
     kCtlProgress = 192,   // work items finished
     kCtlSeedItems = 224,  // items of the first interval placed in the item ring
+    kCtlSpare = 240,      // wavefronts of the launch no item needs so far (signed)
     kCtlArgs = 256,       // a copy of the launch's FlowArgs (16 words)
     kCtlWords = 272
 };
@@ -144,6 +172,9 @@ struct FlowArgs {
                              // parking at all)
     uint32_t backlog;        // items waiting in the item ring above which a filter that
                              // is not urgent is parked
+    uint32_t split_waves;    // wavefronts that a batch too small to fill the GPU is spread
+                             // over, shared by its unfinished filters (0: no splitting)
+    int32_t spare;           // wavefronts launched beyond one per group of 64 particles
     uint32_t pad;
     uint64_t stall_ticks;  // wall-clock ticks without a finished item before a
                            // waiting wavefront gives up (a scheduler fault)
@@ -179,9 +210,19 @@ constexpr int kFlowMinWavesPerCu = 16;
 // Ring capacity for F slots of nchunk groups of 64 particles.
 inline uint32_t flow_ring_capacity(size_t F, int nchunk) {
     const size_t need = 2 * F * (size_t)nchunk;
-    uint32_t c = 1024;
+    // one interval of every filter, and the at most 4096 items (split_waves)
+    // that splitting may add to it
+    uint32_t c = 8192;
     while ((size_t)c < need && c < (1u << 31)) c <<= 1;
     return c;
+}
+
+// Room in the per-interval schedule's item list for `chunks` groups of 64.  A
+// list below kSplitChunks groups may split them (kSplitWavesPerCu per CU more
+// items at most); larger ones fill the GPU without.
+constexpr size_t kSplitChunks = 2048;
+inline size_t item_list_capacity(size_t chunks) {
+    return chunks < kSplitChunks ? kSplitChunks + 4096 : chunks;
 }
 
 // Per-request setup / results.  A request is n_theta rate vectors against M

@@ -88,7 +88,7 @@ template <int UMAX, int RMAX, int PREC>
 __host__ __device__ constexpr int item_lds_words() {
     return kPoolLdsWords + kSortBuckets +
            (LdsNet<RMAX>::on ? ((PREC == LIK_FP32_MIXED ? RMAX : 2 * RMAX) + 3) / 4 * 4 +
-                                   RMAX * nu_row_words<UMAX>()
+                                   (RMAX + 1) * nu_row_words<UMAX>()
                              : 0);
 }
 
@@ -300,6 +300,47 @@ __device__ __forceinline__ void ssa_event(const NetT &net, const Real *c, int *x
     }
 }
 
+// The same event of draw (nl, u2) without branches, for the lanes whose `lim`
+// is their observation time; a lane that stops gets -infinity there and keeps
+// its state by adding zero changes (it may be given any particle's draw: its
+// clock, finite, stays above lim).  True where the particle goes on.  The
+// choice of the reaction does not wait for the waiting time.  Same operations
+// as ssa_event.  Bound by the latency of its dependent chain (propensities,
+// quotient, comparison): four particles of the immigration-death network run
+// 178 ns per event (draws included), against 264 ns with ssa_event's branches.
+__device__ __forceinline__ bool stopped(double lim) { return lim == -__builtin_inf(); }
+template <class NetT, int UMAX, int RMAX, int W, int PREC, class Real>
+__device__ __forceinline__ bool event_masked(const NetT &net, const Real *c, int *x, Real *S,
+                                             double &lim, uint32_t event_cap, double &clock,
+                                             uint32_t &n, int &st, Real &a0_end,
+                                             const uint32_t *nu_tab, Real nl, Real u2) {
+    if (LdsNet<RMAX>::on) asm volatile("" ::: "memory");
+    const Real s = running_sums<NetT, RMAX, Real>(net, c, x, S);
+    a0_end = s;  // a lane that has stopped forms its last total again
+    const Real target = u2 * s;
+    const double tau = (double)(nl / s);
+    const double after = clock + tau;
+    const bool capped = n >= event_cap;
+    const bool on = !(after > lim) & (s > (Real)0) & !capped;
+    if (__builtin_amdgcn_ballot_w64(capped) != 0ull)
+        if (capped && s > (Real)0 && !stopped(lim))
+            st = st > LIK_STATUS_EVENT_CAP ? st : LIK_STATUS_EVENT_CAP;
+    if (LdsNet<RMAX>::on) {
+        const int rs = select_index<NetT, RMAX, Real>(net, S, target);
+        apply_row<UMAX>(net.U, nu_tab, on ? rs : net.R, x);  // row R: no change
+    } else {
+        uint32_t sel[W];
+        select_reaction<NetT, RMAX, W, Real>(net, S, target, sel);
+#pragma unroll
+        for (int w = 0; w < W; ++w) sel[w] = on ? sel[w] : 0u;
+        apply_change<UMAX, W>(net.U, sel, x);
+    }
+    clock = on ? after : clock;
+    n += on ? 1u : 0u;
+    lim = on ? lim : -__builtin_inf();
+    return on;
+}
+
 // ---------------------------------------------------------------------------
 // propagate: for every particle of the item's pool, gather its ancestor's
 // counts, run Gillespie's direct method from the previous observation time
@@ -307,7 +348,7 @@ __device__ __forceinline__ void ssa_event(const NetT &net, const Real *c, int *x
 // k_weigh).
 //
 // A work item is a pool of G * 64 consecutive particles of one filter (G set
-// per filter by k_order).  Each lane runs one event per loop iteration; a lane
+// per filter by k_order), or where the GPU would stand idle a part of 64.  Each lane runs one event per loop iteration; a lane
 // whose particle has reached the observation time finishes it and takes the
 // next particle of the pool (ballot + rank among the idle lanes), so lanes are
 // not held up by the slowest particle of a fixed group of 64.  Which lane runs
@@ -337,9 +378,9 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     const int H = wave_uniform(d.H);
     const int Hp = wave_uniform(d.Hp);
     const int lane = lane_id();
-    const int p0 = (int)(item & 63u) * kPropBlock;
-    const int pool = wave_uniform((int)e.pool[f]);  // (priority << 6) | (G - 1)
-    const int p1 = min(p0 + ((pool & 63) + 1) * kPropBlock, H);
+    const int pool = wave_uniform((int)e.pool[f]);  // (priority << 6) | item code
+    const int p0 = (int)(item & 63u) * code_unit(pool & 63);
+    const int p1 = min(p0 + code_span(pool & 63), H);
 
     const double t_start = wave_uniform((t == 0) ? d.t0 : d.t_obs[t - 1]);
     const double t_end = wave_uniform(d.t_obs[t]);
@@ -375,14 +416,15 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     if (kLds) {
         for (int r = lane; r < R; r += kPropBlock) c_lds[r] = (Real)d.theta[r];
         // net changes as signed bytes, from the network's packed fields
-        for (int q = lane; q < R * kRow; q += kPropBlock) {
+        // (row R: no change)
+        for (int q = lane; q < (R + 1) * kRow; q += kPropBlock) {
             const int r = q / kRow, w = q - r * kRow;
             uint32_t word = 0u;
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const int u = 4 * w + k;
                 int v = 0;
-                if (u < U)
+                if (u < U && r < R)
                     v = nu_bytes(U) ? (int)(signed char)(net.nu[r][0] >> (8 * u))
                                     : __builtin_amdgcn_sbfe(net.nu[r][u >> 3], 4 * (u & 7), 4);
                 word |= ((uint32_t)v & 0xFFu) << (8 * k);
@@ -489,7 +531,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
         __syncthreads();  // the workgroup is this one wavefront
     }
 
-    int x[UMAX];
+    int x[UMAX] = {};  // (lanes without a particle compute on empty counts)
     double clock = t_start;
     uint32_t n = 0;
     int j = p0 + lane;  // the lane's particle
@@ -543,7 +585,8 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     } else if ((pool >> 6) == 1) {
         __builtin_amdgcn_s_setprio(1);
     }
-    for (;;) {
+    // (an item of at most 32 particles goes to the drain at once)
+    while (p1 - p0 > kPropBlock / 2) {
         if (have)
             ssa_event<NetT, UMAX, RMAX, W, PREC, Real>(
                 net, c, x, S, t_end, event_cap, clock, n, st, a0_end, have, nu_tab,
@@ -586,6 +629,9 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     // the block of events n + 2 (l mod D) and n + 2 (l mod D) + 1).  A draw
     // depends on (n, j) only, so every event uses the numbers it would have
     // drawn itself; draws beyond a particle's end are left unused.
+    //
+    // Here the chain of one particle's events sets the pace, not the issue
+    // rate: the event is computed without branches (event_masked).
     using Draw = EventDraw<PREC>;
     Draw *dbuf = reinterpret_cast<Draw *>(pool_x);                    // [64]
     uint32_t *xn = reinterpret_cast<uint32_t *>(dbuf + kPropBlock);  // [32]: running lanes' n
@@ -593,9 +639,9 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     static_assert(sizeof(Draw) * kPropBlock + 4 * kPropBlock <= 4 * kPoolLdsWords,
                   "drain buffers fit the pool's LDS");
     __syncthreads();  // every read of the staged counts is done
-    for (;;) {
-        const uint64_t busy = __ballot(have);
-        if (busy == 0ull) break;
+    uint64_t busy = __builtin_amdgcn_ballot_w64(have);
+    double lim = have ? t_end : -__builtin_inf();
+    while (busy != 0ull) {
         const int k = (int)__popcll(busy);  // <= 32
         const int D = kPropBlock / k;       // >= 2
         // floor(l / D) as (l * ceil(2^16 / D)) >> 16: the product exceeds
@@ -604,7 +650,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
         const int m = (0x10000 + D - 1) / D;
         const int rank = (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(busy >> 32),
                                                         __builtin_amdgcn_mbcnt_lo((uint32_t)busy, 0u));
-        if (have) {
+        if (!stopped(lim)) {
             xn[rank] = n;
             xj[rank] = j;
         }
@@ -615,14 +661,18 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
                 xn[r] + (uint32_t)((lane - r * D) * (PREC == LIK_FP32_MIXED ? 2 : 1)),
                 (uint32_t)xj[r], c2, c3, k0, k1);
         __syncthreads();
-        const int slot = rank * D;
-#pragma unroll 1
+        // lanes that have stopped read a running lane's draws: every draw
+        // that reaches event_masked is a valid one
+        const Draw *own = dbuf + min(rank, k - 1) * D;
         for (int i = 0; i < D; ++i) {
-            if (have)
-                ssa_event<NetT, UMAX, RMAX, W, PREC, Real>(net, c, x, S, t_end, event_cap, clock,
-                                                           n, st, a0_end, have, nu_tab,
-                                                           [&] { return dbuf[slot + i]; });
-            if (__ballot(have) == 0ull) break;
+            const Draw dr = own[i];
+            bool on = event_masked<NetT, UMAX, RMAX, W, PREC, Real>(
+                net, c, x, S, lim, event_cap, clock, n, st, a0_end, nu_tab, dr.nl, dr.u2);
+            if constexpr (PREC == LIK_FP32_MIXED)
+                on = event_masked<NetT, UMAX, RMAX, W, PREC, Real>(
+                    net, c, x, S, lim, event_cap, clock, n, st, a0_end, nu_tab, dr.nl1, dr.u21);
+            busy = __builtin_amdgcn_ballot_w64(on);
+            if (busy == 0ull) break;
         }
         __syncthreads();  // the draws are read before the next round writes
     }

@@ -72,7 +72,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     std::vector<lik_network *> nets;
     std::vector<ReqPlan> plan((size_t)n_req);
     std::vector<int32_t> fstart((size_t)n_req + 1), outoff((size_t)n_req + 1);
-    int64_t F = 0, chunks = 0, items_max = 0, n_out = 0;
+    int64_t F = 0, chunks = 0, items_max = 0, intervals = 0, n_out = 0;
     double work = 0.0;
     int h_max = 1, t_max = 0, umax = 4, rmax = 8;
     for (int k = 0; k < n_req; ++k) {
@@ -103,6 +103,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
         n_out += q.n_theta;
         chunks += p.F * (p.Hp / 64);
         items_max += (int64_t)q.n_theta * p.total * (p.Hp / 64);
+        intervals += (int64_t)q.n_theta * p.total;
         work += (double)p.F * p.H * p.t_max;
         h_max = std::max(h_max, p.H);
         t_max = std::max(t_max, p.t_max);
@@ -122,7 +123,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     const size_t o_tcur = c.take((size_t)F * 4), o_fst = c.take((size_t)F * 4);
     const size_t o_ffl = c.take((size_t)F * 4), o_cost = c.take((size_t)F * 4);
     const size_t o_pool = c.take((size_t)F), o_fll = c.take((size_t)F * 8);
-    const size_t o_fev = c.take((size_t)F * 8), o_items = c.take((size_t)chunks * 4);
+    const size_t o_fev = c.take((size_t)F * 8), o_items = c.take(item_list_capacity((size_t)chunks) * 4);
     const size_t o_icount = c.take(kMaxGroups * 4), o_icur = c.take(kMaxGroups * 4);
     const size_t o_ocount = c.take(kMaxGroups * kCostKeys * 4);
     const size_t o_opos = c.take(kMaxGroups * kCostKeys * 4), o_octl = c.take(2 * 4);
@@ -280,6 +281,8 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     fa.mask = ring_cap - 1;
     fa.n_slots = (int32_t)F;
     fa.g_par = (int32_t)std::max<int64_t>(1, chunks / std::max<uint32_t>(e.pool_min_items, 1u));
+    fa.split_waves = split_waves();
+    fa.spare = flow_spare(intervals, h_max, items_max);
     fa.urgent_events = tu.urgent_events;
     fa.backlog = std::max(compute_units(), 1u) * tu.backlog_per_cu;
     int dev_id = 0, khz = 0;
@@ -296,8 +299,12 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
         std::vector<int64_t> need(nets.size(), 0);
         for (int k = 0; k < n_req; ++k)
             need[(size_t)plan[(size_t)k].group] += plan[(size_t)k].F * (plan[(size_t)k].Hp / 64);
+        std::vector<int64_t> slots(nets.size(), 0);
+        for (int k = 0; k < n_req; ++k) slots[(size_t)plan[(size_t)k].group] += plan[(size_t)k].F;
+        if (!tu.persistent) e.split_goal = split_goal((size_t)F, (size_t)chunks);
         uint32_t off = 0;
         for (size_t g = 0; g < nets.size(); ++g) {
+            need[g] += slots[g] * e.split_goal;  // room for split items
             GroupLaunch &G = groups[g];
             G.netargs = generic_netargs(*nets[g]);
             G.umax = nets[g]->umax;
@@ -338,7 +345,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
         }
         if (flow) {
             if ((err = launch_flow_setup(e, fa, s)) != hipSuccess) { rc = hip_fail(err, "flow setup"); break; }
-            const unsigned waves = (unsigned)std::max<int64_t>(items_max, 1);
+            const unsigned waves = (unsigned)std::max<int64_t>(items_max + fa.spare, 1);
             hipEvent_t t0 = timing_begin(s);
             if (spec_multi) {
                 EngineArgs ea = e;

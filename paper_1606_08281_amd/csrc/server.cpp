@@ -426,16 +426,23 @@ void worker_main(lik_server *S) {
         }
         // one iteration over every resident filter
         GroupLaunch launches[kMaxGroups];
-        unsigned need[kMaxGroups] = {0};
+        unsigned need[kMaxGroups] = {0}, filters[kMaxGroups] = {0};
+        unsigned chunks = 0, running = 0;
         int32_t h_max = 1;
         for (auto &r : S->resident)
             if (r->iterations_left > 0) {
                 need[r->group] += (unsigned)(r->F() * (r->Hp / 64));
+                filters[r->group] += (unsigned)r->F();
+                chunks += (unsigned)(r->F() * (r->Hp / 64));
+                running += (unsigned)r->F();
                 h_max = std::max(h_max, r->H);
             }
         S->e.h_max = h_max;
+        S->e.split_goal = S->persistent ? 0 : split_goal(running, chunks);
         unsigned off = 0;
         for (int g = 0; g < kMaxGroups; ++g) {
+            // a slot has at most 64 items (its share of the item list)
+            need[g] = std::min(need[g] + filters[g] * (unsigned)S->e.split_goal, filters[g] * 64u);
             launches[g] = S->groups[g].launch;
             launches[g].max_items = need[g];
             S->e.group_off[g] = off;
@@ -443,7 +450,7 @@ void worker_main(lik_server *S) {
         }
         S->e.f_lo = 0;
         S->e.f_hi = (int32_t)S->slots.high_water();
-        S->e.pool_chunks = off;  // groups of 64 particles of the slots still running
+        S->e.pool_chunks = chunks;  // groups of 64 particles of the slots still running
         if (engine_iteration(S->e, launches, kMaxGroups, S->stream) != hipSuccess)
             S->worker_error = "iteration launch failed";
         S->n_iterations += 1;
