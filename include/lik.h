@@ -81,7 +81,8 @@ extern "C" {
                             block), binary64 clock and weights */
 
 /* propagation kernel variants (lik_eval_opts.kernel) */
-#define LIK_KERNEL_AUTO 0        /* specialised when the batch amortises compiling it */
+#define LIK_KERNEL_AUTO 0        /* specialised when the batch amortises compiling it, or
+                                    when it is loaded or in the disk cache already */
 #define LIK_KERNEL_GENERIC 1     /* reaction tables read at run time */
 #define LIK_KERNEL_SPECIALIZED 2 /* reaction tables compiled in (hipRTC, cached on disk) */
 
@@ -389,7 +390,7 @@ typedef struct lik_server_stats {
  *     at most 2^26 filters (theta x trajectory pairs) in all.
  *   tuning: work partitioning and schedule (NULL: the defaults).
  *   kernel: LIK_KERNEL_* (AUTO: specialised when the batch amortises the
- *     compile).
+ *     compile or none is needed).
  *   loglik_out [sum of n_theta] host: request k's values at offset
  *     sum_{j<k} reqs[j].n_theta, as lik_eval_batch writes them; status_out
  *     likewise, or NULL.

@@ -499,12 +499,17 @@ hipError_t lik::engine_iteration(const EngineArgs &e, const GroupLaunch *groups,
 }
 
 bool lik::choose_specialized(lik_network &net, int precision, int variant, double work,
-                             hipFunction_t *fn, std::string *err) {
+                             bool may_load, hipFunction_t *fn, std::string *err) {
     *fn = nullptr;
-    // Specialise when the work is large enough to amortise a compile (or a
-    // cache read): >= 2^22 particle-intervals.
+    // Specialise when the work is large enough to amortise a compile (1.3 to
+    // 2.2 s): >= 2^22 particle-intervals.  Where none is needed -- the kernel is
+    // loaded, or a precompile left it in the disk cache -- any batch gains: the
+    // generic kernel's event takes 509 ns in the latency-bound case where the
+    // specialised one takes 193 ns (64 immigration-death particles), and for
+    // 18 reactions of 9 species about 100 times as long.
     if (variant == LIK_KERNEL_SPECIALIZED ||
-        (variant == LIK_KERNEL_AUTO && work >= 4194304.0)) {
+        (variant == LIK_KERNEL_AUTO &&
+         (work >= 4194304.0 || specialized_available(net, precision, may_load)))) {
         *fn = specialized_kernel(net, precision, err);
         if (!*fn && variant == LIK_KERNEL_SPECIALIZED) return false;
     }
@@ -613,13 +618,20 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
     G.rmax = net->rmax;
     G.precision = precision;
     std::string err;
+    hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+    bool may_load = true;
+    if (!no_alloc && (hipStreamIsCapturing((hipStream_t)stream, &capture) != hipSuccess ||
+                      capture != hipStreamCaptureStatusNone)) {
+        (void)hipGetLastError();
+        may_load = false;
+    }
     if (no_alloc) {
         if (variant != LIK_KERNEL_GENERIC) G.spec = loaded_specialized_kernel(*net, precision);
         if (!G.spec && variant == LIK_KERNEL_SPECIALIZED)
             return fail(LIK_EINVAL, "the specialised kernel is not loaded on this device yet "
                                     "(an earlier call of another entry point loads it)");
-    } else if (!choose_specialized(*net, precision, variant, (double)F * H * t_max, &G.spec,
-                                   &err)) {
+    } else if (!choose_specialized(*net, precision, variant, (double)F * H * t_max, may_load,
+                                   &G.spec, &err)) {
         return fail(LIK_EDEVICE, "specialised kernel unavailable: " + err);
     }
     G.persistent = net->tuning.persistent != 0 && net->R <= kPersistentMaxR;

@@ -38,6 +38,7 @@ struct lik_network {
         hipFunction_t flow = nullptr;        // lik_flow_spec
     };
     std::map<std::pair<int, int>, SpecKernels> spec;
+    std::string spec_path[2];  // their files in the disk cache, per precision (once formed)
     // captured launch sequences of lik_eval_batch_device (LIK_FLAG_GRAPH)
     struct Graph {
         hipGraph_t graph = nullptr;
@@ -68,6 +69,11 @@ hipFunction_t specialized_kernel(lik_network &net, int precision, std::string *e
 // The specialised kernel if an earlier call has already loaded it on the
 // current device, else nullptr; never compiles or loads (no allocation).
 hipFunction_t loaded_specialized_kernel(lik_network &net, int precision, int kind = kSpecItem);
+
+// Whether the specialised kernel costs no compile: loaded on the current
+// device, or (may_load: the caller can load a module) in the disk cache.
+bool specialized_available(lik_network &net, int precision, bool may_load);
+bool specialized_multi_available(const std::vector<lik_network *> &nets, int precision);
 
 // The flow kernel for filters of several networks (group g = nets[g]), each
 // item running its network's specialised body; compiled with hipRTC (cached on
@@ -141,7 +147,9 @@ hipError_t engine_iteration(const EngineArgs &e, const GroupLaunch *groups, int 
 
 // The specialised kernel if the variant and the amount of work call for it.
 // Returns false only when LIK_KERNEL_SPECIALIZED was asked for and failed.
-bool choose_specialized(lik_network &net, int precision, int variant, double work,
+// may_load: a batch below the compile's threshold may load a cached kernel (not
+// while its stream is being captured, which a module load would break).
+bool choose_specialized(lik_network &net, int precision, int variant, double work, bool may_load,
                         hipFunction_t *fn, std::string *err);
 
 const void *generic_netargs(const lik_network &net);

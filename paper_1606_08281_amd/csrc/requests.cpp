@@ -258,7 +258,9 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     if (flow) {
         int per_cu = 0;
         const bool want_spec = kernel == LIK_KERNEL_SPECIALIZED ||
-                               (kernel == LIK_KERNEL_AUTO && work >= 4194304.0);
+                               (kernel == LIK_KERNEL_AUTO &&
+                                (work >= 4194304.0 ||
+                                 specialized_multi_available(nets, precision)));
         if (want_spec) {
             spec_multi = specialized_multi_kernel(nets, precision, &msg);
             if (!spec_multi && kernel == LIK_KERNEL_SPECIALIZED) {
@@ -311,7 +313,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
             G.rmax = nets[g]->rmax;
             G.precision = precision;
             G.max_items = (unsigned)need[g];
-            if (!choose_specialized(*nets[g], precision, kernel, work, &G.spec, &msg)) {
+            if (!choose_specialized(*nets[g], precision, kernel, work, true, &G.spec, &msg)) {
                 (void)hipFree(dev);
                 return fail(LIK_EDEVICE, "specialised kernel unavailable: " + msg);
             }

@@ -258,8 +258,8 @@ bool specialized_code(const lik_network &net, int precision, std::vector<char> *
     return code_for_source(src, code, path_out, err);
 }
 
-bool code_for_source(const std::string &src, std::vector<char> *code, std::string *path_out,
-                     std::string *err) {
+// The disk cache's file for a generated source.
+std::string cache_path(const std::string &src) {
     // the key covers everything the code object depends on: the generated
     // source, the embedded kernel headers, the options and the compiler
     std::string key = src;
@@ -273,9 +273,12 @@ bool code_for_source(const std::string &src, std::vector<char> *code, std::strin
     key += " hiprtc " + std::to_string(rtc_major) + "." + std::to_string(rtc_minor);
     char hex[32];
     snprintf(hex, sizeof(hex), "%016llx", (unsigned long long)fnv1a(key));
-    const std::string dir = cache_dir();
-    const std::string path = dir + "/prop_" + hex + ".co";
+    return cache_dir() + "/prop_" + hex + ".co";
+}
 
+bool code_for_source(const std::string &src, std::vector<char> *code, std::string *path_out,
+                     std::string *err) {
+    const std::string dir = cache_dir(), path = cache_path(src);
     *path_out = path;
     if (read_file(path, code)) return true;
     if (!compile(src, code, err)) return false;
@@ -348,12 +351,36 @@ hipFunction_t loaded_specialized_kernel(lik_network &net, int precision, int kin
     return kind == kSpecPersistent ? k.persistent : kind == kSpecFlow ? k.flow : k.item;
 }
 
+bool specialized_available(lik_network &net, int precision, bool may_load) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    std::lock_guard<std::mutex> g(net.spec_lock);
+    if (net.spec.count({dev, precision})) return true;
+    if (!may_load) return false;
+    std::string &path = net.spec_path[precision == LIK_FP32_MIXED ? 1 : 0];
+    if (path.empty()) path = cache_path(specialized_source(net, precision));
+    return access(path.c_str(), R_OK) == 0;
+}
+
 namespace {
 // Multi-network flow kernels, per (device, source): loaded once and kept for
 // the life of the process (a set of networks has no handle that owns them).
 std::mutex g_multi_mu;
 std::map<std::pair<int, std::string>, std::pair<hipModule_t, hipFunction_t>> g_multi;
+std::map<std::string, std::string> g_multi_path;  // source -> its file in the disk cache
 }  // namespace
+
+bool specialized_multi_available(const std::vector<lik_network *> &nets, int precision) {
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    const std::string src = specialized_multi_source(nets, precision);
+    std::lock_guard<std::mutex> g(g_multi_mu);
+    if (g_multi.count({dev, src})) return true;
+    if (g_multi_path.size() > 64) g_multi_path.clear();
+    std::string &path = g_multi_path[src];
+    if (path.empty()) path = cache_path(src);
+    return access(path.c_str(), R_OK) == 0;
+}
 
 bool rtc_code(const std::string &src, std::vector<char> *code, std::string *err) {
     std::string path;

@@ -1,0 +1,105 @@
+"""Batches too small to fill the GPU: an interval cut into items of fewer than
+64 particles, and the kernel the automatic choice takes, against the oracle
+and against the generic kernel.  Event counts, final particle counts and
+statuses bit for bit; log-likelihoods to 1e-9 relative (the weights' sum is
+the only freedom)."""
+import numpy as np
+import pytest
+
+from paper_1606_08281_amd import workloads as W
+from test_gpu_parity import _gpu, _oracle, _say, assert_parity
+
+pytestmark = pytest.mark.gpu
+
+# around the item sizes 4, 8, 16, 32 and 64, and the largest filter
+SIZES = [1, 5, 31, 33, 63, 65, 250, 1000, 4096]
+
+
+@pytest.mark.parametrize("kernel", [1, 2])
+@pytest.mark.parametrize("precision", [0, 1])
+def test_split_items(orc, precision, kernel):
+    """One filter at a time (the most splitting): every item size and ragged
+    last items, both schedules; 150 and more events per particle and interval."""
+    wl = W.immigration_death_workload(1, t_obs=[5.0, 10.0, 15.0])
+    theta = np.array([[30.0, 0.1]])
+    for H in SIZES:
+        ref = _oracle(orc, wl, theta=theta, H=H, precision=precision)
+        for schedule in (1, 0):
+            _say("split items H", H, "precision", precision, "kernel", kernel, "schedule", schedule)
+            assert_parity(_gpu(wl, theta=theta, H=H, precision=precision, kernel=kernel,
+                               tuning={"schedule": schedule}), ref)
+
+
+@pytest.mark.parametrize("schedule", [1, 0])
+def test_split_items_event_cap(orc, schedule):
+    """The event cap reached inside split items: the theta's status."""
+    wl = W.immigration_death_workload(1, t_obs=[5.0, 10.0])
+    theta = np.array([[30.0, 0.1], [20.0, 0.1]])
+    for cap in (1, 63, 64, 150, 400):
+        ref = _oracle(orc, wl, theta=theta, H=40, event_cap=cap)
+        _say("split items cap", cap, "schedule", schedule)
+        assert_parity(_gpu(wl, theta=theta, H=40, event_cap=cap, kernel=2,
+                           tuning={"schedule": schedule}), ref)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+def test_split_items_large_network(orc, precision):
+    """Rates and net changes in LDS: stopped lanes take the row without a change."""
+    wl = W.random_network_workload(n_theta=3, n_particles=45, n_obs=3)
+    _say("split items 20x40 precision", precision)
+    ref = _oracle(orc, wl, precision=precision)
+    for kernel in (1, 2):
+        assert_parity(_gpu(wl, precision=precision, kernel=kernel), ref)
+
+
+def test_automatic_kernel_choice(monkeypatch, tmp_path):
+    """A batch below the compile's threshold: generic without a compiled kernel,
+    specialised once one is in the disk cache; the results are the same."""
+    from paper_1606_08281_amd import lik
+    monkeypatch.setenv("LIK_KERNEL_CACHE", str(tmp_path))
+    wl = W.telegraph_workload(n_theta=5, n_traj=2, n_obs=6, n_particles=130)
+
+    def run(net, kernel=lik.KERNEL_AUTO):
+        return lik.eval_batch(net, wl.obs_kind, wl.observed, wl.sigma, wl.theta, wl.trajectories,
+                              wl.n_particles, wl.seed, aux=True, kernel=kernel)
+
+    net = lik.Network(wl.net.orders, wl.net.stoich)
+    before = run(net)
+    assert not list(tmp_path.iterdir())
+    net.precompile()
+    after, fresh = run(net), run(lik.Network(wl.net.orders, wl.net.stoich))
+    reqs = [dict(net=net, obs_kind=wl.obs_kind, observed=wl.observed, sigma=wl.sigma,
+                 theta=wl.theta, trajectories=wl.trajectories, n_particles=wl.n_particles,
+                 seed=wl.seed)]
+    one = lik.eval_requests(reqs)[0][0]
+    lik.precompile_requests([net])
+    two = lik.eval_requests(reqs)[0][0]
+    for got in (after, fresh, run(net, lik.KERNEL_GENERIC)):
+        for k in before:
+            assert np.array_equal(before[k], got[k]), k
+    assert np.array_equal(one, before["loglik"]) and np.array_equal(two, before["loglik"])
+
+
+def test_automatic_kernel_choice_under_capture():
+    """A small batch captured by its caller before any kernel was loaded, then
+    replayed with eager calls between: no module load inside the capture."""
+    import torch
+    from paper_1606_08281_amd import lik
+    wl = W.telegraph_workload(n_theta=3, n_traj=2, n_obs=5, n_particles=70)
+    net = lik.Network(wl.net.orders, wl.net.stoich)
+    net.precompile()
+    db = lik.DeviceBatch(net, wl.obs_kind, wl.observed, wl.sigma, wl.trajectories, wl.n_theta,
+                         wl.n_particles)
+    theta = torch.from_numpy(wl.theta).cuda()
+    graph = torch.cuda.CUDAGraph()
+    torch.cuda.synchronize()
+    with torch.cuda.graph(graph, capture_error_mode="global"):
+        db.run(theta, wl.seed)
+    for _ in range(3):
+        db.loglik.zero_()
+        graph.replay()
+        torch.cuda.synchronize()
+        replayed = db.loglik.clone()
+        eager, _ = db.run(theta, wl.seed)
+        torch.cuda.synchronize()
+        assert torch.equal(replayed, eager)
