@@ -59,12 +59,12 @@ uint32_t lik::split_waves() { return std::min(compute_units() * kSplitWavesPerCu
 
 int32_t lik::split_goal(size_t slots, size_t chunks) {
     if (slots == 0 || chunks >= kSplitChunks) return 0;
-    return (int32_t)std::min<size_t>(split_waves() / slots, 64);
+    return (int32_t)(split_waves() / slots);
 }
 
 int32_t lik::flow_spare(int64_t intervals, int h_max, int64_t items_max) {
     const int64_t least = kPropBlock >> kSplitMax;  // particles of the smallest item
-    const int64_t most = intervals * std::min<int64_t>(64, (h_max + least - 1) / least);
+    const int64_t most = intervals * ((h_max + least - 1) / least);
     // an empty wavefront costs its dispatch: bounded
     return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, 1 << 18));
 }
@@ -599,6 +599,7 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
                                   flow_ring_capacity(F, nchunk));
     L.e.f_lo = 0;
     L.e.f_hi = (int32_t)F;
+    L.e.item_shift = item_shift_for(F);
     L.e.pool_min = net->tuning.pool_min;
     L.e.pool_max = net->tuning.pool_max;
     L.e.pool_events = net->tuning.pool_events;

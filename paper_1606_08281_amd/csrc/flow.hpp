@@ -34,12 +34,19 @@
 // append, and so wait only behind a short ring.  No deadlock: a filter is
 // parked only while items wait, and the last of them to finish un-parks.
 // At most one interval of items per filter is outstanding: its groups of 64,
-// or when split no more than its share of split_waves.  The share only grows
-// as filters finish, so at most sum(groups of 64) + split_waves <= capacity
-// entries sit in a ring and a producer never waits for a slot that no
-// wavefront has claimed.  Hand-offs between wavefronts (item results before the
-// weighing, the weighing's state before the next items) are agent-scope
-// release/acquire pairs.
+// and split items beyond them counted in kCtlExtra, so at most
+// sum(groups of 64) + split_waves <= capacity entries sit in a ring and a
+// producer never waits for a slot that no wavefront has claimed.
+//
+// Hand-offs between wavefronts (item results before the weighing, the
+// weighing's state before the next items): everything a later wavefront reads
+// is stored at agent scope, through the L2 cache of the storing XCD; the giver
+// waits for its stores (stores_done) and then makes the hand-off known with an
+// atomic operation; the taker acquires at agent scope.  No store of this
+// kernel stays dirty in an L2 while another XCD may write or read its address
+// (the weights' scratch included).  Releasing plain stores instead wrote the
+// XCD's whole L2 back, three times per item: 326 -> 322 ms for 1024 telegraph
+// rate vectors in FP64, 213 -> 166 ms for 512 in FP32-mixed without.
 #pragma once
 #ifndef __HIPCC_RTC__
 #include <hip/hip_runtime.h>
@@ -97,21 +104,22 @@ __device__ __forceinline__ bool ring_wait(const FlowArgs &fa, int r, uint32_t po
     }
 }
 
-// Reserves n positions of ring r and writes one entry per lane below n (a
-// lane waits until its slot is free for the position).  The caller has
+// Reserves n positions of ring r and writes entry first + k step at the k-th of
+// them (a lane waits until its slot is free for the position).  The caller has
 // released what the entries' readers need.
-__device__ __forceinline__ void ring_put(const FlowArgs &fa, int r, int n, uint32_t entry_of_lane,
-                                         int lane) {
+__device__ __forceinline__ void ring_put(const FlowArgs &fa, int r, int n, uint32_t first,
+                                         uint32_t step, int lane) {
     uint32_t base = 0;
     if (lane == 0)
         base = __hip_atomic_fetch_add(&fa.ctl[kCtlTail + 64 * r], (uint32_t)n, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
     base = __builtin_amdgcn_readfirstlane(base);  // lane 0's: every lane is active
-    if (lane < n) {
-        const uint32_t pos = base + (uint32_t)lane;
+    for (int k = lane; k < n; k += 64) {
+        const uint32_t pos = base + (uint32_t)k;
         uint64_t ent;
         if (ring_wait(fa, r, pos, pos, &ent, false))
-            __hip_atomic_store(ring_slot(fa, r, pos), ((uint64_t)(pos + 1u) << 32) | entry_of_lane,
+            __hip_atomic_store(ring_slot(fa, r, pos),
+                               ((uint64_t)(pos + 1u) << 32) | (first + (uint32_t)k * step),
                                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
 }
@@ -145,33 +153,64 @@ __device__ __forceinline__ int32_t item_backlog(const FlowArgs &fa) {
 // to the item ring.
 __device__ __forceinline__ void emit_items(const EngineArgs &e, const FlowArgs &fa, int f,
                                            int code, int lane) {
-    const int n_items = code_items(code, e.desc[f].H);  // <= 64: one lane per item
-    ring_put(fa, kRingItems, n_items, ((uint32_t)f << 6) | (uint32_t)(lane * code_step(code)),
-             lane);
+    ring_put(fa, kRingItems, code_items(code, e.desc[f].H), (uint32_t)f << e.item_shift,
+             (uint32_t)code_step(code), lane);
 }
 
-// Items each filter's interval should be cut into so that the filters not
-// yet finished fill the GPU (0: no splitting).
-__device__ __forceinline__ int split_goal(const FlowArgs &fa, int finished) {
-    return (int)(fa.split_waves / (uint32_t)max(fa.n_slots - finished, 1));
+// A filter's part of what is left of the batch: the expected events of one of
+// its particles (c: of its whole next interval) times its intervals left, from
+// interval t on -- the length of its chain.
+__device__ __forceinline__ uint64_t flow_weight(const FilterDesc &d, uint32_t c, int t) {
+    return (uint64_t)min(c / (uint32_t)d.H, 1u << 20) * (uint64_t)(d.T - t);
+}
+__device__ __forceinline__ uint64_t add_weight(const FlowArgs &fa, uint64_t by) {  // returns the sum
+    return by + __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(&fa.ctl[kCtlWeight]), by,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint32_t ctl_add(const FlowArgs &fa, int w, uint32_t by) {
+    return __hip_atomic_fetch_add(&fa.ctl[w], by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// Items the next interval of a filter of weight w should be cut into: its
+// share, by weight, of split_waves, as far as the items running now leave
+// room (none while items wait).  A batch that keeps the GPU busy is not split:
+// an item of 32 particles issues 1.3 times the instructions of its half of 64.
+__device__ __forceinline__ int flow_goal(const FlowArgs &fa, uint64_t w, uint64_t sum,
+                                         int nchunk) {
+    const uint32_t head = ctl_load(fa, kCtlHead + 64 * kRingItems);
+    const uint32_t tail = ctl_load(fa, kCtlTail + 64 * kRingItems);
+    const uint32_t done = ctl_load(fa, kCtlProgress);
+    if ((int32_t)(tail - head) > 0 || sum == 0) return 0;
+    const int room = (int)fa.split_waves - (int)(tail - done);
+    if (room <= 0) return 0;
+    return min((int)((double)fa.split_waves * ((double)w / (double)sum)), nchunk + room);
 }
 
 // The launch has one wavefront per group of 64 particles of every interval
 // and fa.spare more; kCtlSpare counts those that no item needs.  A filter
 // whose interval takes fewer items than groups gives the rest; one that is
-// split takes the difference, or is not split when too few are left, so an
-// item always finds a wavefront.  One lane only.
+// split takes the difference, or is not split when too few are left (an item
+// always finds a wavefront) or when the split items outstanding would exceed
+// split_waves (a ring slot is always free).  One lane only.
 __device__ __forceinline__ int settle_spare(const FlowArgs &fa, int code, int H, int nchunk) {
     const int need = code_items(code, H) - nchunk;
-    uint32_t *spare = &fa.ctl[kCtlSpare];
-    if (need < 0)
-        __hip_atomic_fetch_add(spare, (uint32_t)-need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (need < 0) ctl_add(fa, kCtlSpare, (uint32_t)-need);
     if (need <= 0) return code;
-    const int had = (int)__hip_atomic_fetch_sub(spare, (uint32_t)need, __ATOMIC_RELAXED,
-                                                __HIP_MEMORY_SCOPE_AGENT);
-    if (had >= need) return code;
-    __hip_atomic_fetch_add(spare, (uint32_t)need, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if ((int)ctl_add(fa, kCtlExtra, (uint32_t)need) + need <= (int)fa.split_waves) {
+        if ((int)ctl_add(fa, kCtlSpare, (uint32_t)-need) >= need) return code;
+        ctl_add(fa, kCtlSpare, (uint32_t)need);
+    }
+    ctl_add(fa, kCtlExtra, (uint32_t)-need);
     return 0;
+}
+
+// A filter's interval (item code `code`, expected events c, interval t) is
+// over: its share of the split items and of the weights.  One lane only.
+__device__ __forceinline__ uint64_t leave_interval(const FlowArgs &fa, const FilterDesc &d,
+                                                   int code, uint32_t c, int t) {
+    const int extra = code_items(code, d.H) - (d.Hp >> 6);
+    if (extra > 0) ctl_add(fa, kCtlExtra, (uint32_t)-extra);
+    return flow_weight(d, c, t);
 }
 
 // While the item ring is short and filters are parked, takes one parked
@@ -197,12 +236,9 @@ __device__ __forceinline__ bool flow_unpark(const EngineArgs &e, const FlowArgs 
     }
     f = __builtin_amdgcn_readfirstlane(f);
     if (f < 0) return false;
-    // acquire the parked filter's state; release it again to the items' takers
+    // acquire the parked filter's state (its items' takers acquire it themselves)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    const int code = (int)e.pool[f];
-    __threadfence();
-    __syncthreads();
-    emit_items(e, fa, f, code, lane);
+    emit_items(e, fa, f, (int)e.pool[f], lane);
     return true;
 }
 
@@ -239,16 +275,18 @@ __device__ __forceinline__ int item_wait(const FlowArgs &fa, uint32_t pos, uint6
     }
 }
 
-// Number of resampling points j*Q + rho (j = 0, 1, ...) below x:
+// Number of resampling points j*Q + rho (j = 0, 1, ...) below x, at most H:
 // ceil((x - rho) / Q) for x > rho.  The quotient (at most H) is estimated in
-// binary64 and then made exact with integer products (x < 2^57, Q < 2^45).
-__device__ __forceinline__ uint64_t points_below(uint64_t x, uint64_t rho, uint64_t Q) {
+// binary64 (inv_Q: the nearest to 1 / Q) and then made exact with integer
+// products (x < 2^57, Q < 2^45).
+__device__ __forceinline__ uint32_t points_below(uint64_t x, uint64_t rho, uint64_t Q,
+                                                 double inv_Q, uint32_t H) {
     if (x <= rho) return 0;
     const uint64_t y = x - rho - 1;  // n = floor(y / Q) + 1
-    uint64_t m = (uint64_t)((double)y / (double)Q);
+    uint32_t m = (uint32_t)((double)y * inv_Q);
     while (m > 0 && m * Q > y) --m;
     while ((m + 1) * Q <= y) ++m;
-    return m + 1;
+    return min(m + 1, H);
 }
 
 // Weighing of filter f after its interval tcur[f], by one wavefront, with
@@ -256,30 +294,50 @@ __device__ __forceinline__ uint64_t points_below(uint64_t x, uint64_t rho, uint6
 // run over particles lane-strided, so every lane's loads are independent.
 // The one order-dependent sum, S = sum e_j, follows k_weigh's order: each
 // lane adds its particles j = lane + 64 k in increasing k, then one
-// butterfly over the lanes.  The slot's lw array holds l_j, then e_j.  Resampling is taken from the particles' side: with
+// butterfly over the lanes.  The slot's lw array holds l_j, then e_j.  Resampling is taken from the
+// particles' side: with
 // J(x) = #{j >= 0 : j Q + rho < x}, particle i is the ancestor of exactly
 // the j in [J(H C_i), J(H C_{i+1})) -- the same a_j = min{i : H C_{i+1} >
-// j Q + rho} as the search over j, found without dependent loads.
+// j Q + rho} as the search over j, found without dependent loads.  Every
+// particle with offspring marks its first output in LDS (`lds`, the item's
+// buffer), and a running maximum over the outputs fills the rest, so a
+// filter whose weight sits on one particle takes no longer than another.
+//
+// On a filter's chain of intervals nothing hides this step: it is bound by
+// the latency of its loads (the counts come from other wavefronts through the
+// last-level cache), so each pass takes kB groups of 64 particles at a time,
+// their loads issued together, and scans run on DPP adds, not through LDS.
+// A near-eventless interval of one filter (hand-offs included) went from 75 to
+// 48 us at 1000 particles and from 250 to 125 us at 4096.
 // Returns true when the filter goes on to another interval; *cost receives
 // its expected events.
 __device__ __forceinline__ bool flow_weigh(const EngineArgs &e, int f, double *logy,
-                                           uint32_t *cost) {
+                                           uint32_t *lds, uint32_t *cost) {
     const FilterDesc &d = e.desc[f];
     const int lane = lane_id();
     const int t = e.tcur[f];
     const int H = d.H;
+    const int status = e.fstatus[f];
+    auto stop_filter = [&](double ll) {
+        store_global(e.tcur, (uint32_t)f, t + 1);
+        store_global(e.fll, (uint32_t)f, ll);
+        store_global(e.fflags, (uint32_t)f, e.fflags[f] | kFlagStopped);
+    };
     {
         uint64_t evs = 0;
-        for (int j = lane; j < H; j += 64) evs += d.pev[j];
-        evs = wave_sum_u64(evs, lane);
-        if (lane == 0) e.fevents[f] += evs;
-    }
-    if (e.fstatus[f] != LIK_STATUS_OK) {
-        if (lane == 0) {
-            e.tcur[f] = t + 1;
-            e.fll[f] = __builtin_nan("");
-            e.fflags[f] |= kFlagStopped;
+        constexpr int kE = 16;
+        for (int base = lane; base < H; base += 64 * kE) {
+            uint32_t v[kE];
+#pragma unroll
+            for (int k = 0; k < kE; ++k) v[k] = base + 64 * k < H ? d.pev[base + 64 * k] : 0u;
+#pragma unroll
+            for (int k = 0; k < kE; ++k) evs += v[k];
         }
+        evs = wave_sum_u64(evs, lane);
+        if (lane == 0) store_global(e.fevents, (uint32_t)f, e.fevents[f] + evs);
+    }
+    if (status != LIK_STATUS_OK) {
+        if (lane == 0) stop_filter(__builtin_nan(""));
         return false;
     }
     const int32_t *xs = (t & 1) ? d.xa : d.xb;  // counts at the observation time
@@ -289,145 +347,175 @@ __device__ __forceinline__ bool flow_weigh(const EngineArgs &e, int f, double *l
     double *w = d.lw;
     const ObsParams op = obs_params(d);
 
-    // Per-particle passes take kB particles per lane at a time, their loads
-    // issued together (a load cannot move above an earlier iteration's store
-    // to another array, so one particle at a time waits on each load).
-    constexpr int kB = 2;
+    // kB particles per lane at a time, their loads issued together.
+    constexpr int kB = 4;
     // log-weights and their maximum
     double mx = -__builtin_inf();
-    // counts of the first observed component: the next pair's are loaded
-    // before this pair's log-weights are stored
-    const int32_t *x0s = xs + (size_t)d.obs_species[0] * d.Hp;
-    int c0[kB];
-#pragma unroll
-    for (int k = 0; k < kB; ++k) c0[k] = lane + 64 * k < H ? x0s[lane + 64 * k] : 0;
     if (op.kind == LIK_OBS_FLUORESCENCE) {
         // one particle at a time: its count-dependent variance makes the term
-        // longer, and pairs would raise the kernel's register count
+        // longer, and groups would raise the kernel's register count
         for (int j = lane; j < H; j += 64) {
             const double l = obs_logweight(d, op, xs, j, logy, yt);
-            w[j] = l;
+            store_global(w, (uint32_t)j, l);
             mx = fmax(mx, l);
         }
-    } else
-    for (int base = lane; base < H; base += 64 * kB) {
-        double l[kB];
-        bool on[kB];
-        int n0[kB];
-#pragma unroll
-        for (int k = 0; k < kB; ++k) {
-            l[k] = 0.0;
-            on[k] = base + 64 * k < H;
-            const int jn = base + 64 * (kB + k);
-            n0[k] = jn < H ? x0s[jn] : 0;
-        }
-        for (int o = 0; o < d.P; ++o) {
-            const int32_t *xo = xs + (size_t)d.obs_species[o] * d.Hp;
-            int cnt[kB];
-#pragma unroll
-            for (int k = 0; k < kB; ++k) cnt[k] = o == 0 ? c0[k] : on[k] ? xo[base + 64 * k] : 0;
-#pragma unroll
-            for (int k = 0; k < kB; ++k)
-                if (on[k]) on[k] = obs_term<false>(op, o, cnt[k], logy, yt, l[k]);
-        }
-#pragma unroll
-        for (int k = 0; k < kB; ++k) c0[k] = n0[k];
-#pragma unroll
-        for (int k = 0; k < kB; ++k)
-            if (base + 64 * k < H) {
-                w[base + 64 * k] = l[k];
-                mx = fmax(mx, l[k]);
-            }
-    }
-    mx = wave_max(mx, lane);
-    if (mx == -__builtin_inf()) {
-        if (lane == 0) {
-            e.tcur[f] = t + 1;
-            e.fll[f] = -__builtin_inf();
-            e.fflags[f] |= kFlagStopped;
-        }
-        return false;
-    }
-    // e_j = exp(l_j - mx) in place, and S = sum e_j in k_weigh's order: each
-    // lane's particles in increasing j, then one butterfly; the next pair's
-    // loads are issued before this pair's stores
-    double s = 0.0;
-    {
-        double v[kB];
-#pragma unroll
-        for (int k = 0; k < kB; ++k) v[k] = lane + 64 * k < H ? w[lane + 64 * k] : 0.0;
+    } else {
         for (int base = lane; base < H; base += 64 * kB) {
-            double nx[kB];
+            double l[kB];
+            bool on[kB];
 #pragma unroll
             for (int k = 0; k < kB; ++k) {
-                const int jn = base + 64 * (kB + k);
-                nx[k] = jn < H ? w[jn] : 0.0;
+                l[k] = 0.0;
+                on[k] = base + 64 * k < H;
+            }
+            for (int o = 0; o < d.P; ++o) {
+                const int32_t *xo = xs + (size_t)d.obs_species[o] * d.Hp;
+                int cnt[kB];
+#pragma unroll
+                for (int k = 0; k < kB; ++k) cnt[k] = base + 64 * k < H ? xo[base + 64 * k] : 0;
+#pragma unroll
+                for (int k = 0; k < kB; ++k)
+                    if (on[k]) on[k] = obs_term<false>(op, o, cnt[k], logy, yt, l[k]);
             }
 #pragma unroll
             for (int k = 0; k < kB; ++k)
                 if (base + 64 * k < H) {
-                    const double ej = dexp_nonpos(v[k] - mx);
-                    w[base + 64 * k] = ej;
-                    s += ej;
+                    store_global(w, (uint32_t)(base + 64 * k), l[k]);
+                    mx = fmax(mx, l[k]);
                 }
-#pragma unroll
-            for (int k = 0; k < kB; ++k) v[k] = nx[k];
         }
+    }
+    mx = wave_max(mx, lane);
+    if (mx == -__builtin_inf()) {
+        if (lane == 0) stop_filter(-__builtin_inf());
+        return false;
+    }
+    // e_j = exp(l_j - mx) in place, S = sum e_j in k_weigh's order (each
+    // lane's particles in increasing j, then one butterfly), and the total Q of
+    // q_j = floor(e_j 2^32); the next batch is loaded before this one's stores
+    double s = 0.0;
+    uint64_t Q = 0;
+    double v[kB];
+#pragma unroll
+    for (int k = 0; k < kB; ++k) v[k] = lane + 64 * k < H ? w[lane + 64 * k] : 0.0;
+    for (int base = lane; base < H; base += 64 * kB) {
+        double nx[kB];
+#pragma unroll
+        for (int k = 0; k < kB; ++k) {
+            const int jn = base + 64 * (kB + k);
+            nx[k] = jn < H ? w[jn] : 0.0;
+        }
+#pragma unroll
+        for (int k = 0; k < kB; ++k)
+            if (base + 64 * k < H) {
+                const double ej = dexp_nonpos(v[k] - mx);
+                store_global(w, (uint32_t)(base + 64 * k), ej);
+                s += ej;
+                Q += (uint64_t)(ej * 4294967296.0);
+            }
+#pragma unroll
+        for (int k = 0; k < kB; ++k) v[k] = nx[k];
     }
     const double S = wave_sum(s, lane);
     if (lane == 0) {
-        e.fll[f] = e.fll[f] + loglik_increment(d, mx, S, yt);
-        e.tcur[f] = t + 1;
+        store_global(e.fll, (uint32_t)f, e.fll[f] + loglik_increment(d, mx, S, yt));
+        store_global(e.tcur, (uint32_t)f, t + 1);
     }
     if (t + 1 >= d.T) return false;
 
-    // q_j = floor(e_j 2^32) and their total Q
-    uint64_t Q = 0;
-    for (int j = lane; j < H; j += 64) Q += (uint64_t)(w[j] * 4294967296.0);
     Q = wave_sum_u64(Q, lane);
+    const double inv_Q = 1.0 / (double)Q;
     const uint64_t rho = __umul64hi(resample_word(d, t), Q);
     const uint64_t Hu = (uint64_t)H;
-    // each group of 64 particles: prefix sums C_i, C_{i+1} (carried over
-    // groups), then every particle writes the outputs it is the ancestor of
-    float pred = 0.0f;  // sum of the ancestors' total propensities
-    uint64_t carry = 0;    // C at the group's first particle
-    uint64_t carry_j = 0;  // J(H C) there
-    double v[kB];
-    float a0[kB];
+    // kG groups of 64 particles at a time: prefix sums C_{i+1} (carried over
+    // groups) and outputs [J(H C_i), J(H C_{i+1})), the first of them marked
+    // (index + 1, 16 bits) in the window of outputs [w0, w1) that LDS holds;
+    // a full window is filled and written, and the next one begun
+    constexpr int kG = 4;
+    constexpr int kWin = 2 * kPoolLdsWords;  // 3072 outputs
+    uint16_t *mark = reinterpret_cast<uint16_t *>(lds);
+    float pred = 0.0f;     // sum of the ancestors' total propensities
+    uint64_t carry = 0;    // C at the batch's first particle
+    uint32_t carry_j = 0;  // J(H C) there
+    uint32_t last = 0;     // mark carried into the window
+    int w0 = 0, w1 = min(H, kWin);
+    auto clear = [&]() {
+        for (int q = lane; q < (w1 - w0 + 1) / 2; q += 64) lds[q] = 0u;
+        __syncthreads();  // the workgroup is this one wavefront
+    };
+    clear();
+    static_assert(kG == kB, "v holds a batch");
+    float a0[kG];
 #pragma unroll
-    for (int k = 0; k < kB; ++k) {
+    for (int k = 0; k < kG; ++k) {
         const int i = 64 * k + lane;
         v[k] = i < H ? w[i] : 0.0;
         a0[k] = i < H ? d.pa0[i] : 0.0f;
     }
-    for (int b0 = 0; b0 < H; b0 += 64 * kB) {
-        // the next groups' weights, loaded before this group's stores
-        double nv[kB];
-        float na[kB];
+    for (int b0 = 0; b0 < H; b0 += 64 * kG) {
+        // the next batch's weights, loaded before this one's stores
+        double nv[kG];
+        float na[kG];
 #pragma unroll
-        for (int k = 0; k < kB; ++k) {
-            const int i = b0 + 64 * (kB + k) + lane;
+        for (int k = 0; k < kG; ++k) {
+            const int i = b0 + 64 * (kG + k) + lane;
             nv[k] = i < H ? w[i] : 0.0;
             na[k] = i < H ? d.pa0[i] : 0.0f;
         }
+        uint64_t incl[kG];
 #pragma unroll
-        for (int k = 0; k < kB; ++k) {
-            const int i = b0 + 64 * k + lane;
-            const uint64_t q = i < H ? (uint64_t)(v[k] * 4294967296.0) : 0;
-            const uint64_t incl = carry + wave_incl_scan_u64(q, lane);  // C_{i+1}
-            // J(H C_{i+1}); J(H C_i) is the previous particle's
-            const uint64_t j_hi = i < H ? min(points_below(Hu * incl, rho, Q), Hu) : Hu;
-            const uint64_t prev = lane_read(j_hi, lane > 0 ? lane - 1 : 0);
-            const uint64_t j_lo = lane > 0 ? prev : carry_j;
-            if (i < H) {
-                for (uint64_t j = j_lo; j < j_hi; ++j) d.anc[j] = i;
-                pred += (float)(j_hi - j_lo) * a0[k];
-            }
-            carry = lane_read(incl, 63);
-            carry_j = lane_read(j_hi, 63);
+        for (int k = 0; k < kG; ++k)
+            incl[k] = wave_incl_scan_u64((uint64_t)(v[k] * 4294967296.0));
+        uint32_t j_lo[kG], j_hi[kG];
+#pragma unroll
+        for (int k = 0; k < kG; ++k) {
+            incl[k] += carry;  // C_{i+1}
+            carry = lane_last(incl[k]);
         }
 #pragma unroll
-        for (int k = 0; k < kB; ++k) {
+        for (int k = 0; k < kG; ++k) {
+            // J(H C_{i+1}); J(H C_i) is the previous particle's
+            j_hi[k] = b0 + 64 * k + lane < H
+                          ? points_below(Hu * incl[k], rho, Q, inv_Q, (uint32_t)H)
+                          : (uint32_t)H;
+            j_lo[k] = lane_prev(j_hi[k], carry_j);
+            carry_j = lane_last(j_hi[k]);
+            if (b0 + 64 * k + lane < H) pred += (float)(j_hi[k] - j_lo[k]) * a0[k];
+        }
+        for (;;) {
+#pragma unroll
+            for (int k = 0; k < kG; ++k)
+                if (j_lo[k] < j_hi[k] && (int)j_lo[k] >= w0 && (int)j_lo[k] < w1)
+                    mark[j_lo[k] - (uint32_t)w0] = (uint16_t)(b0 + 64 * k + lane + 1);
+            if ((int)carry_j < w1) break;
+            // every mark below w1 is set: fill the window
+            __syncthreads();
+            for (int q0 = 0; q0 < w1 - w0; q0 += 64 * kG) {
+                uint32_t m[kG];
+#pragma unroll
+                for (int k = 0; k < kG; ++k) {
+                    const int q = q0 + 64 * k + lane;
+                    m[k] = wave_incl_max_u32(q < w1 - w0 ? mark[q] : 0u);
+                }
+#pragma unroll
+                for (int k = 0; k < kG; ++k) {
+                    const int q = q0 + 64 * k + lane;
+                    m[k] = max(m[k], last);
+                    last = lane_last(m[k]);
+                    if (q < w1 - w0) store_global(d.anc, (uint32_t)(w0 + q), (int32_t)m[k] - 1);
+                }
+            }
+            __syncthreads();
+            if (w1 >= H) {
+                w1 = 1 << 30;  // every output is written: the particles left have none
+                break;
+            }
+            w0 = w1;
+            w1 = min(H, w0 + kWin);
+            clear();
+        }
+#pragma unroll
+        for (int k = 0; k < kG; ++k) {
             v[k] = nv[k];
             a0[k] = na[k];
         }
@@ -447,26 +535,31 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
     // lane 0 wrote tcur: its reading decides, for every lane
     const int H = e.desc[f].H;
     int code = 0;
-    if (lane == 0)
-        code = settle_spare(fa,
-                            item_code(e, f, cost, fa.g_par,
-                                      split_goal(fa, (int)ctl_load(fa, kCtlFinished))),
-                            H, e.desc[f].Hp >> 6);
+    if (lane == 0) {
+        const FilterDesc &d = e.desc[f];
+        const int t = e.tcur[f], nchunk = d.Hp >> 6;
+        const uint64_t was = leave_interval(fa, d, e.pool[f], e.cost[f], t - 1);
+        const uint64_t w = flow_weight(d, cost, t);
+        const uint64_t sum = add_weight(fa, w - was);
+        code = settle_spare(fa, item_code(e, f, cost, fa.g_par, flow_goal(fa, w, sum, nchunk)), H,
+                            nchunk);
+    }
     code = __builtin_amdgcn_readfirstlane(code);
     const int n_items = code_items(code, H);
     const int park = __builtin_amdgcn_readfirstlane(
         (int)(!flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
     if (lane == 0) {
-        e.cost[f] = cost;
-        e.pool[f] = (uint8_t)code;
+        store_global(e.cost, (uint32_t)f, cost);
+        store_global(e.pool, (uint32_t)f, (uint8_t)code);
         __hip_atomic_store(&fa.remaining[f], (uint32_t)n_items, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
-    // release: everything above before the items (or the parked entry) are visible
-    __threadfence();
+    // everything above (agent-scope stores) before the items or the parked
+    // entry are visible
+    stores_done();
     __syncthreads();
     if (park)
-        ring_put(fa, kRingParked, 1, (uint32_t)f, lane);
+        ring_put(fa, kRingParked, 1, (uint32_t)f, 0u, lane);
     else
         emit_items(e, fa, f, code, lane);
 }
@@ -491,9 +584,11 @@ __device__ __forceinline__ const EngineArgs &reload_engine_args() {
 
 // run(item) runs one work item (the propagation of its pool); a launch over
 // several networks picks the item's network inside it.
+// lds: the item's buffer, at least kPoolLdsWords words (the weighing uses it
+// after the item).
 template <class RunItem>
 __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArgs &fa,
-                                              RunItem &&run) {
+                                              uint32_t *lds, RunItem &&run) {
     __shared__ double logy[LIK_MAX_OBSERVED];
     // the wavefronts beyond the batch's last item start after it is done
     if ((int)__builtin_amdgcn_readfirstlane(ctl_load(fa, kCtlFinished)) >= fa.n_slots) return;
@@ -518,11 +613,12 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
     // acquire: the filter's state written before the item was published
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     const uint32_t item = __builtin_amdgcn_readfirstlane((uint32_t)ent);
-    const int f = (int)(item >> 6);
+    const int f = (int)(item >> e.item_shift);
     run(item);
 
-    // release: this item's results before the filter's count goes down
-    __threadfence();
+    // this item's results (agent-scope stores) before the filter's count goes
+    // down
+    stores_done();
     __syncthreads();
     // From here on the engine's arguments are read again from the kernel's
     // argument segment, where used (the fields loaded at the kernel's start
@@ -530,7 +626,7 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
     const EngineArgs &ec = reload_engine_args();
     uint32_t left = 0;
     if (lane_id() == 0) {
-        left = __hip_atomic_fetch_sub(&fa.remaining[f], 1u, __ATOMIC_ACQ_REL,
+        left = __hip_atomic_fetch_sub(&fa.remaining[f], 1u, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
         __hip_atomic_fetch_add(&fa.ctl[kCtlProgress], 1u, __ATOMIC_RELAXED,
                                __HIP_MEMORY_SCOPE_AGENT);
@@ -543,15 +639,15 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
     // the last item of the interval: weigh the filter with every item's results
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     uint32_t cost = 0;
-    if (flow_weigh(ec, f, logy, &cost)) {
+    if (flow_weigh(ec, f, logy, lds, &cost)) {
         flow_push(ec, fa, f, cost);
         flow_unpark_some(ec, fa, lane_id());
     } else {
-        __threadfence();
-        __syncthreads();
         if (lane_id() == 0) {
-            if (ec.fdone) ec.fdone[f] = wall_clock64();
-            __hip_atomic_fetch_add(&fa.ctl[kCtlFinished], 1u, __ATOMIC_RELEASE,
+            add_weight(fa, 0 - leave_interval(fa, ec.desc[f], ec.pool[f], ec.cost[f],
+                                              ec.tcur[f] - 1));
+            if (ec.fdone) store_global(ec.fdone, (uint32_t)f, (uint64_t)wall_clock64());
+            __hip_atomic_fetch_add(&fa.ctl[kCtlFinished], 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);
         }
         flow_unpark_some(ec, fa, lane_id());
@@ -562,7 +658,7 @@ template <class NetT, int UMAX, int RMAX, int W, int PREC>
 __device__ __forceinline__ void flow_run(const EngineArgs &e, const FlowArgs &fa,
                                          const NetT &net) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[item_lds_words<UMAX, RMAX, PREC>()];
-    flow_run_with(e, fa,
+    flow_run_with(e, fa, lds,
                   [&](uint32_t item) { run_item<NetT, UMAX, RMAX, W, PREC>(e, net, item, lds); });
 }
 

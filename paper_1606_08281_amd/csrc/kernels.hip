@@ -232,7 +232,7 @@ __global__ __launch_bounds__(64 * kMaxGroups) void k_order_scan(EngineArgs e) {
     for (int k0 = 0; k0 < kCostKeys; k0 += 64) {
         const int k = k0 + lane;
         const uint32_t h = k < kCostKeys ? e.order_count[g * kCostKeys + k] : 0u;
-        const uint64_t incl = wave_incl_scan_u64(h, lane);
+        const uint64_t incl = wave_incl_scan_u64(h);
         if (k < kCostKeys) {
             e.order_pos[g * kCostKeys + k] = (uint32_t)(run + incl - h);
             e.order_count[g * kCostKeys + k] = 0u;
@@ -274,7 +274,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
     if (!on) return;
     const uint32_t pos = lcount[gk] + local;
     for (uint32_t q = 0; q < n_items; ++q)
-        e.items[pos + q] = ((uint32_t)f << 6) | (q * (uint32_t)code_step(code));
+        e.items[pos + q] = ((uint32_t)f << e.item_shift) | (q * (uint32_t)code_step(code));
     // Wavefront priority: the slots whose particles are expected to need
     // the most events are the ones the iteration waits for; their
     // wavefronts issue first on a SIMD they share with lighter ones.
@@ -336,10 +336,11 @@ __global__ void k_flow_seed(EngineArgs e, FlowArgs fa, int pass) {
         if (pass == 0) atomicAdd(&fa.ctl[kCtlFinished], 1u);
         return;
     }
-    int code = item_code(e, f, e.cost[f], fa.g_par, split_goal(fa, 0));
+    int code = item_code(e, f, e.cost[f], fa.g_par, (int)(fa.split_waves / (uint32_t)fa.n_slots));
     const bool urgent = flow_urgent(e, fa, f, e.cost[f], code < kSplitCode ? code + 1 : 1);
     if (urgent != (pass == 0)) return;
     code = settle_spare(fa, code, e.desc[f].H, e.desc[f].Hp >> 6);
+    add_weight(fa, flow_weight(e.desc[f], e.cost[f], 0));
     const int n_items = code_items(code, e.desc[f].H);
     e.pool[f] = (uint8_t)code;
     fa.remaining[f] = (uint32_t)n_items;
@@ -351,7 +352,7 @@ __global__ void k_flow_seed(EngineArgs e, FlowArgs fa, int pass) {
     for (int k = 0; k < n; ++k) {
         const uint32_t pos = base + (uint32_t)k;
         const uint32_t entry =
-            park ? (uint32_t)f : (((uint32_t)f << 6) | (uint32_t)(k * code_step(code)));
+            park ? (uint32_t)f : (((uint32_t)f << e.item_shift) | (uint32_t)(k * code_step(code)));
         ring[pos & fa.mask] = ((uint64_t)(pos + 1u) << 32) | entry;
     }
 }
@@ -371,8 +372,8 @@ template <int UMAX, int RMAX, int W, int PREC>
 __global__ __launch_bounds__(kPropBlock) void k_flow_multi(EngineArgs e, const FlowArgs *fa,
                                                            const NetArgs<RMAX, W> *nets) {
     __shared__ __attribute__((aligned(16))) uint32_t lds[item_lds_words<UMAX, RMAX, PREC>()];
-    flow_run_with(e, *fa, [&](uint32_t item) {
-        const int g = __builtin_amdgcn_readfirstlane(e.desc[item >> 6].group);
+    flow_run_with(e, *fa, lds, [&](uint32_t item) {
+        const int g = __builtin_amdgcn_readfirstlane(e.desc[item >> e.item_shift].group);
         const NetArgs<RMAX, W> &src = nets[g];
         NetArgs<RMAX, W> net;
         net.U = __builtin_amdgcn_readfirstlane(src.U);
@@ -500,7 +501,7 @@ __global__ __launch_bounds__(kWeighBlock) void k_weigh(EngineArgs e) {
     }
 
     // exclusive scan of the per-thread sums (thread order = particle order)
-    const uint64_t incl = wave_incl_scan_u64(qsum, lane);
+    const uint64_t incl = wave_incl_scan_u64(qsum);
     if (lane == 63) redu[wave] = incl;
     __syncthreads();
     uint64_t base = incl - qsum;

@@ -36,7 +36,7 @@ constexpr int kSortBuckets = 64;  // half octaves of the expected cost, below th
 // are G - 1 for items of G * 64 particles (G <= 16: pool_lds_cap of one
 // species); code kSplitCode + s is an item of 64 >> s particles, whose idle
 // lanes draw the running lanes' coming events ahead of time, so a particle's
-// events follow each other sooner.  A slot has at most 64 items.
+// events follow each other sooner.
 constexpr int kSplitCode = 32;
 constexpr int kSplitMax = 4;  // items of 32, 16, 8 or 4 particles
 __host__ __device__ constexpr int code_span(int code) {  // particles per item
@@ -45,8 +45,8 @@ __host__ __device__ constexpr int code_span(int code) {  // particles per item
 __host__ __device__ constexpr int code_items(int code, int H) {
     return (H + code_span(code) - 1) / code_span(code);
 }
-// Step between the chunk numbers (low 6 bits) of a slot's consecutive items,
-// and the particles a chunk number counts.
+// A work item is (slot << item_shift) | chunk number.  Step between the chunk
+// numbers of a slot's consecutive items, and the particles one counts.
 __host__ __device__ constexpr int code_step(int code) { return code < kSplitCode ? code + 1 : 1; }
 __host__ __device__ constexpr int code_unit(int code) {
     return code < kSplitCode ? kPropBlock : code_span(code);
@@ -54,8 +54,18 @@ __host__ __device__ constexpr int code_unit(int code) {
 // Items are split only for particles expected to need this many events: a
 // shorter item is over before its hand-off is.
 constexpr uint32_t kSplitMinEvents = 48;
-// Wavefronts per compute unit that splitting fills the GPU to.
-constexpr uint32_t kSplitWavesPerCu = 12;
+// Wavefronts per compute unit that splitting fills the GPU to: one per SIMD.
+// A drain event issues for 60 % of its latency, so more of them on a SIMD only
+// wait for each other (64 immigration-death filters of 256: 8.4 ms unsplit,
+// 5.1 / 5.5 / 6.0 / 6.8 ms at 2 / 4 / 6 / 12; 256 Lac-Gfp rate vectors: 754 ms
+// unsplit, 673 / 661 / 657 / 640).
+constexpr uint32_t kSplitWavesPerCu = 4;
+
+// Bits of the chunk number: 10 (4096 particles in items of 4) where the slot
+// numbers leave them, else 6 (groups of 64, no finer splitting than 64 items).
+__host__ __device__ constexpr int item_shift_for(uint64_t slots) {
+    return slots <= (1ull << 22) ? 10 : 6;
+}
 
 // Reaction kinds after validation of the reactant orders.
 enum : int32_t { kOrder0 = 0, kOrder1 = 1, kOrder2Homo = 2, kOrder2Hetero = 3 };
@@ -114,7 +124,7 @@ struct EngineArgs {
     uint64_t *fevents;        // [slots] SSA events applied
     uint32_t *cost;           // [slots] expected events of the next interval (ordering key)
     uint8_t *pool;            // [slots] (wave priority << 6) | item code
-    uint32_t *items;          // propagation work items (slot << 6 | chunk), grouped
+    uint32_t *items;          // propagation work items (slot << item_shift | chunk), grouped
     uint32_t *item_count;     // [kMaxGroups] items written per group
     uint32_t *item_cursor;    // [kMaxGroups] next item to take (persistent kernels)
     // Ordering of an iteration's work (three passes: count, scan, place).
@@ -135,6 +145,7 @@ struct EngineArgs {
     int32_t priority;         // raise the wave priority of the heaviest slots
     uint32_t pool_min_items;  // work items an iteration keeps before pools grow
     int32_t h_max;            // most particles of any active slot (LDS of k_weigh)
+    int32_t item_shift;       // bits of a work item's chunk number (item_shift_for)
     int32_t split_goal;       // per-interval schedule: items a slot is cut into, its groups of
                               // 64 particles allowing (0: only by its pool size)
     uint32_t group_off[kMaxGroups];  // first item of each group
@@ -153,6 +164,8 @@ enum : int {
     kCtlProgress = 192,   // work items finished
     kCtlSeedItems = 224,  // items of the first interval placed in the item ring
     kCtlSpare = 240,      // wavefronts of the launch no item needs so far (signed)
+    kCtlExtra = 241,      // items outstanding beyond one per group of 64 (signed)
+    kCtlWeight = 242,     // 64 bits: flow_weight summed over the filters not finished
     kCtlArgs = 256,       // a copy of the launch's FlowArgs (16 words)
     kCtlWords = 272
 };
@@ -173,7 +186,7 @@ struct FlowArgs {
     uint32_t backlog;        // items waiting in the item ring above which a filter that
                              // is not urgent is parked
     uint32_t split_waves;    // wavefronts that a batch too small to fill the GPU is spread
-                             // over, shared by its unfinished filters (0: no splitting)
+                             // over (0: no splitting)
     int32_t spare;           // wavefronts launched beyond one per group of 64 particles
     uint32_t pad;
     uint64_t stall_ticks;  // wall-clock ticks without a finished item before a

@@ -136,12 +136,25 @@ __device__ __forceinline__ void apply_change(int U, const uint32_t *sel, int *x)
 
 // base[i] = v through the global address space (base: device memory), with
 // the byte offset formed in 32 bits: a wave-uniform base stays in scalar
-// registers and the store takes the offset from one vector register.
+// registers and the store takes the offset from one vector register.  An
+// agent-scope (relaxed atomic) store: written through the L2 cache of the
+// storing XCD, so the flow schedule hands particles to a wavefront on another
+// XCD by waiting for its stores (stores_done), without the write-back of the
+// whole L2 that a release of plain stores takes.
 template <class T>
 __device__ __forceinline__ void store_global(T *base, uint32_t i, T v) {
     typedef __attribute__((address_space(1))) char gchar;
     typedef __attribute__((address_space(1))) T gT;
-    *(gT *)((gchar *)base + i * (uint32_t)sizeof(T)) = v;
+    __hip_atomic_store((gT *)((gchar *)base + i * (uint32_t)sizeof(T)), v, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The wavefront's stores so far have reached the point they were sent to:
+// agent-scope stores before are visible to whoever acquires after an atomic
+// operation that follows.
+__device__ __forceinline__ void stores_done() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup");
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
 }
 
 template <bool B, class T, class F>
@@ -369,7 +382,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     // after stores of earlier items, and would otherwise keep them in
     // vector registers through the event loop).
     item = wave_uniform(item);
-    const int f = (int)(item >> 6);
+    const int f = (int)(item >> e.item_shift);
     const FilterDesc &d = e.desc[f];
     const int t = wave_uniform(e.tcur[f]);
 
@@ -379,7 +392,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
     const int Hp = wave_uniform(d.Hp);
     const int lane = lane_id();
     const int pool = wave_uniform((int)e.pool[f]);  // (priority << 6) | item code
-    const int p0 = (int)(item & 63u) * code_unit(pool & 63);
+    const int p0 = (int)(item & ((1u << e.item_shift) - 1u)) * code_unit(pool & 63);
     const int p1 = min(p0 + code_span(pool & 63), H);
 
     const double t_start = wave_uniform((t == 0) ? d.t0 : d.t_obs[t - 1]);
@@ -788,12 +801,12 @@ __device__ __forceinline__ void propagate_persistent(const EngineArgs &e, const 
                         break;
                     }
                     const uint32_t item = __builtin_amdgcn_readfirstlane(items[idx]);
-                    pf = (int)(item >> 6);
+                    pf = (int)(item >> e.item_shift);
                     const FilterDesc &d = e.desc[pf];
                     const int t = __builtin_amdgcn_readfirstlane(e.tcur[pf]);
                     const int H = __builtin_amdgcn_readfirstlane(d.H);
                     p_hp = __builtin_amdgcn_readfirstlane(d.Hp);
-                    p0 = (int)(item & 63u) * kPropBlock;
+                    p0 = (int)(item & ((1u << e.item_shift) - 1u)) * kPropBlock;
                     const int g = (int)(__builtin_amdgcn_readfirstlane(e.pool[pf]) & 63u) + 1;
                     p1 = min(p0 + g * kPropBlock, H);
                     next = p0;

@@ -241,6 +241,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     e.fdone = (uint64_t *)(dev + o_fdone);
     e.f_lo = 0;
     e.f_hi = (int32_t)F;
+    e.item_shift = item_shift_for((uint64_t)F);
     e.pool_min = tu.pool_min;
     e.pool_max = tu.pool_max;
     e.pool_events = tu.pool_events;

@@ -441,8 +441,7 @@ void worker_main(lik_server *S) {
         S->e.split_goal = S->persistent ? 0 : split_goal(running, chunks);
         unsigned off = 0;
         for (int g = 0; g < kMaxGroups; ++g) {
-            // a slot has at most 64 items (its share of the item list)
-            need[g] = std::min(need[g] + filters[g] * (unsigned)S->e.split_goal, filters[g] * 64u);
+            need[g] += filters[g] * (unsigned)S->e.split_goal;  // room for split items
             launches[g] = S->groups[g].launch;
             launches[g].max_items = need[g];
             S->e.group_off[g] = off;
@@ -507,7 +506,7 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     const size_t slots = (size_t)o.max_filters;
     const size_t table = align256(slots * sizeof(FilterDesc)) + 4 * align256(slots * 4) +
                          align256(slots) +
-                         2 * align256(slots * 8) + align256(slots * 64 * 4) +
+                         2 * align256(slots * 8) + align256((slots * 64 + split_waves()) * 4) +
                          2 * align256(kMaxGroups * 4) + align256(slots * 8) +
                          align256(slots * 4) + 2 * align256(kMaxGroups * kCostKeys * 4) +
                          align256(2 * 4);
@@ -535,7 +534,8 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     S->e.pool = (uint8_t *)take(slots);
     S->e.fll = (double *)take(slots * 8);
     S->e.fevents = (uint64_t *)take(slots * 8);
-    S->e.items = (uint32_t *)take(slots * 64 * 4);
+    S->e.items = (uint32_t *)take((slots * 64 + split_waves()) * 4);
+    S->e.item_shift = item_shift_for(slots);
     S->e.item_count = (uint32_t *)take(kMaxGroups * 4);
     S->e.item_cursor = (uint32_t *)take(kMaxGroups * 4);
     S->e.order_count = (uint32_t *)take(kMaxGroups * kCostKeys * 4);

@@ -177,8 +177,8 @@ std::string specialized_multi_source(const std::vector<lik_network *> &nets, int
          "lik::EngineArgs e, const lik::FlowArgs *fa) {\n"
          "  __shared__ __attribute__((aligned(16))) uint32_t lds[lik::kMultiLds"
       << nets.size() - 1 << "];\n"
-         "  lik::flow_run_with(e, *fa, [&](uint32_t item) {\n"
-         "    const int g = __builtin_amdgcn_readfirstlane(e.desc[item >> 6].group);\n"
+         "  lik::flow_run_with(e, *fa, lds, [&](uint32_t item) {\n"
+         "    const int g = __builtin_amdgcn_readfirstlane(e.desc[item >> e.item_shift].group);\n"
          "    switch (g) {\n";
     for (size_t g = 0; g < nets.size(); ++g) {
         const int U = nets[g]->U, R = nets[g]->R, W = (U + 7) / 8;

@@ -42,14 +42,46 @@ __device__ __forceinline__ uint64_t wave_sum_u64(uint64_t v, int lane) {
     return v;
 }
 
-// inclusive prefix sum over the 64 lanes of a wavefront
-__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v, int lane) {
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint64_t o = lane_read(v, lane >= off ? lane - off : lane);
-        if (lane >= off) v += o;
-    }
-    return v;
+// Prefix operations over the 64 lanes (all active) with the cross-lane moves
+// of the vector instructions themselves (DPP): shifts by 1, 2, 4 and 8 inside
+// rows of 16 lanes, then lane 15 of rows 0 and 2 to the next row, then lane 31
+// to the upper half; a lane without a source takes 0.
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint32_t dpp_or_zero(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, ROWS, 0xF, false);
+}
+template <int CTRL, int ROWS>
+__device__ __forceinline__ uint64_t dpp_add(uint64_t v) {
+    const uint32_t lo = dpp_or_zero<CTRL, ROWS>((uint32_t)v);
+    const uint32_t hi = dpp_or_zero<CTRL, ROWS>((uint32_t)(v >> 32));
+    return v + (((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ uint64_t wave_incl_scan_u64(uint64_t v) {
+    v = dpp_add<0x111, 0xF>(v);
+    v = dpp_add<0x112, 0xF>(v);
+    v = dpp_add<0x114, 0xF>(v);
+    v = dpp_add<0x118, 0xF>(v);
+    v = dpp_add<0x142, 0xA>(v);
+    return dpp_add<0x143, 0xC>(v);
+}
+__device__ __forceinline__ uint32_t wave_incl_max_u32(uint32_t v) {
+    v = max(v, dpp_or_zero<0x111, 0xF>(v));
+    v = max(v, dpp_or_zero<0x112, 0xF>(v));
+    v = max(v, dpp_or_zero<0x114, 0xF>(v));
+    v = max(v, dpp_or_zero<0x118, 0xF>(v));
+    v = max(v, dpp_or_zero<0x142, 0xA>(v));
+    return max(v, dpp_or_zero<0x143, 0xC>(v));
+}
+// lane 63's value, to every lane
+__device__ __forceinline__ uint32_t lane_last(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+__device__ __forceinline__ uint64_t lane_last(uint64_t v) {
+    return ((uint64_t)lane_last((uint32_t)(v >> 32)) << 32) | lane_last((uint32_t)v);
+}
+// the previous lane's value; lane 0 takes `first`
+__device__ __forceinline__ uint32_t lane_prev(uint32_t v, uint32_t first) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)first, (int)v, 0x138, 0xF, 0xF, false);
 }
 
 __device__ __forceinline__ bool slot_active(const EngineArgs &e, int f) {
@@ -77,7 +109,7 @@ __device__ __forceinline__ int pool_size(const EngineArgs &e, int f, uint32_t c,
 // Item code of slot f for its coming interval.  The pool size, unless the GPU
 // has room for `goal` items of every slot and the pool size gives fewer: then
 // smaller pools down to one group of 64, and below that items of 32 to 4
-// particles (never more than 64 items).  A slot's interval lasts as long as
+// particles (as far as the chunk number reaches).  A slot's interval lasts as long as
 // its longest particle's chain of events; on an idle GPU fewer particles per
 // wavefront shorten the chain, since the idle lanes draw ahead for the others:
 // one filter of 64 immigration-death particles runs 421 ns per event in one
@@ -89,7 +121,7 @@ __device__ __forceinline__ int item_code(const EngineArgs &e, int f, uint32_t c,
     const int nchunk = e.desc[f].Hp >> 6;
     if ((nchunk + g - 1) / g >= goal || c / (uint32_t)H < kSplitMinEvents) return g - 1;
     if (goal <= nchunk) return max(1, nchunk / goal) - 1;
-    const int most = min(goal, 64);
+    const int most = min(goal, 1 << e.item_shift);
     int code = 0;
 #pragma unroll
     for (int s = 1; s <= kSplitMax; ++s)
