@@ -33,7 +33,12 @@ struct lik_ode_t_ {
     std::vector<int32_t> x0_param;
     // the model-specialised kernel, per device
     std::mutex mu;
-    std::map<int, std::pair<hipModule_t, hipFunction_t>> spec;
+    struct Spec {
+        hipModule_t mod = nullptr;
+        hipFunction_t fn = nullptr;     // lik_ode_spec: one lane per pair
+        hipFunction_t group = nullptr;  // lik_ode_group: 16 or 32 lanes per pair, or null
+    };
+    std::map<int, Spec> spec;
     // the terms and x0_param in device memory, per device (made on first use)
     std::map<int, char *> dev;
 };
@@ -94,6 +99,95 @@ int ode_par_stride(int V) { return V % 2 == 1 || V == LIK_ODE_MAX_PARAMS ? V : V
 // LDS bytes of the specialised kernel's launch: one parameter slot per lane.
 size_t ode_par_lds(int V) { return (size_t)64 * ode_par_stride(V) * sizeof(double); }
 
+// Lanes per pair of the group kernel: 16 up to 16 species, else 32; 0 (no such
+// kernel) where the terms would take more than four rounds of them.
+int ode_group_lanes(const lik_ode_model &m) {
+    const int L = m.n_species <= 16 ? 16 : 32;
+    return m.n_terms <= 4 * L ? L : 0;
+}
+int ode_group_rounds(const lik_ode_model &m) {
+    const int L = ode_group_lanes(m);
+    return (m.n_terms + L - 1) / L;
+}
+size_t ode_group_lds(const lik_ode_model &m) {
+    const int L = ode_group_lanes(m);
+    return (size_t)(64 / L) * (L + ode_group_rounds(m) * L + m.n_params) * sizeof(double);
+}
+
+// The FRET ratio or observed species as an expression over pv and x.
+void emit_obs(std::ostringstream &o, const lik_ode_model &m) {
+    if (m.obs_kind == LIK_ODE_OBS_SPECIES) {
+        o << "    return x[" << m.obs_species << "];\n";
+        return;
+    }
+    auto P = [&](int k) { return "pv[" + std::to_string(m.fret_param[k]) + "]"; };
+    o << "    const double xa = x[" << m.obs_species << "], xb = x[" << m.obs_species2 << "];\n"
+      << "    const double num = (" << P(2) << " * " << P(3) << ") * xa;\n"
+      << "    const double den = (xb + (1.0 - " << P(2) << ") * xa) * " << P(4) << ";\n"
+      << "    return " << P(0) << " * (num / den + " << P(1) << ");\n";
+}
+
+// The tables of ode_run_group's model (struct OdeGroup).
+void emit_group_model(std::ostringstream &o, const lik_ode_model &m) {
+    const int L = ode_group_lanes(m), R = ode_group_rounds(m), U = m.n_species, NT = m.n_terms;
+    auto row = [&](const char *type, const char *name, auto &&value) {
+        o << "  static constexpr " << type << " " << name << "[" << NT << "] = {";
+        for (int k = 0; k < NT; ++k) o << (k ? "," : "") << value(k);
+        o << "};\n";
+    };
+    auto row3 = [&](const char *name, auto &&value) {
+        o << "  static constexpr int " << name << "[" << NT << "][3] = {";
+        for (int k = 0; k < NT; ++k) {
+            o << (k ? "," : "") << "{";
+            for (int f = 0; f < 3; ++f)
+                o << (f ? "," : "") << (f < m.terms[k].n_factors ? value(k, f) : 0);
+            o << "}";
+        }
+        o << "};\n";
+    };
+    std::vector<std::vector<int>> list((size_t)U);
+    for (int k = 0; k < NT; ++k) {
+        if (m.terms[k].from >= 0) list[(size_t)m.terms[k].from].push_back(-(k + 1));
+        if (m.terms[k].to >= 0) list[(size_t)m.terms[k].to].push_back(k + 1);
+    }
+    size_t most = 1;
+    for (auto &v : list) most = std::max(most, v.size());
+    o << "struct OdeGroup {\n  static constexpr int U = " << U << ", NT = " << NT << ", V = "
+      << m.n_params << ", L = " << L << ", ROUNDS = " << R << ", MAXL = " << most << ";\n";
+    row("int", "nf", [&](int k) { return m.terms[k].n_factors; });
+    row("int", "rate_param", [&](int k) { return m.terms[k].rate_param; });
+    row("double", "scale", [&](int k) { return hexd(m.terms[k].rate_scale); });
+    // an input factor reads no species and no parameter
+    auto reads = [&](int k, int f) { return m.terms[k].kind[f] != LIK_ODE_INPUT; };
+    auto divides = [&](int k, int f) {
+        return reads(k, f) && m.terms[k].kind[f] != LIK_ODE_SPECIES;
+    };
+    row3("kind", [&](int k, int f) { return m.terms[k].kind[f]; });
+    row3("sp", [&](int k, int f) { return reads(k, f) ? m.terms[k].species[f] : 0; });
+    row3("par", [&](int k, int f) { return divides(k, f) ? m.terms[k].param[f] : 0; });
+    o << "  static constexpr bool DIV[" << R << "][3] = {";
+    for (int r = 0; r < R; ++r) {
+        o << (r ? "," : "") << "{";
+        for (int f = 0; f < 3; ++f) {
+            bool any = false;
+            for (int k = r * L; k < std::min(NT, (r + 1) * L); ++k)
+                any = any || (f < m.terms[k].n_factors && divides(k, f));
+            o << (f ? "," : "") << (any ? "true" : "false");
+        }
+        o << "}";
+    }
+    o << "};\n  static constexpr int list[" << U << "][" << most << "] = {";
+    for (int u = 0; u < U; ++u) {
+        o << (u ? "," : "") << "{";
+        for (size_t i = 0; i < most; ++i)
+            o << (i ? "," : "") << (i < list[(size_t)u].size() ? list[(size_t)u][i] : 0);
+        o << "}";
+    }
+    o << "};\n  __device__ static double obs(const double *pv, const double *x) {\n    (void)pv;\n";
+    emit_obs(o, m);
+    o << "  }\n};\n";
+}
+
 // The model as code: its flux terms with constant indices (the same
 // operations, in the same order, as OdeGeneric::rhs), the parameters of the
 // lane's current theta read from its slot in LDS (copied there when the lane
@@ -151,49 +245,47 @@ std::string ode_spec_source(const lik_ode_model &m) {
     }
     o << "  }\n  __device__ static double obs(const OdeArgs &, const Params &p, const double *x) {\n"
          "    const double *pv = row(p);\n    (void)pv;\n";
-    if (m.obs_kind == LIK_ODE_OBS_SPECIES) {
-        o << "    return x[" << m.obs_species << "];\n";
-    } else {
-        auto P = [&](int k) { return "pv[" + std::to_string(m.fret_param[k]) + "]"; };
-        o << "    const double xa = x[" << m.obs_species << "], xb = x[" << m.obs_species2 << "];\n"
-          << "    const double num = (" << P(2) << " * " << P(3) << ") * xa;\n"
-          << "    const double den = (xb + (1.0 - " << P(2) << ") * xa) * " << P(4) << ";\n"
-          << "    return " << P(0) << " * (num / den + " << P(1) << ");\n";
-    }
-    o << "  }\n};\n}  // namespace lik\n"
+    emit_obs(o, m);
+    o << "  }\n};\n";
+    if (ode_group_lanes(m)) emit_group_model(o, m);
+    o << "}  // namespace lik\n"
          "extern \"C\" __global__ void __launch_bounds__(64) lik_ode_spec(lik::OdeArgs a) {\n"
          "  lik::ode_run<lik::OdeSpec>(a);\n}\n";
+    if (ode_group_lanes(m))
+        o << "extern \"C\" __global__ void __launch_bounds__(64) lik_ode_group(lik::OdeArgs a) {\n"
+             "  lik::ode_run_group<lik::OdeGroup>(a, lik_ode_par);\n}\n";
     return o.str();
 }
 
-// The specialised kernel on the current device (compiled or read from the
-// disk cache on first use); nullptr with *err on failure.
-hipFunction_t ode_spec_kernel(lik_ode_t_ &md, std::string *err) {
+// The specialised kernels on the current device (compiled or read from the
+// disk cache on first use); no function with *err on failure.
+lik_ode_t_::Spec ode_spec_kernel(lik_ode_t_ &md, std::string *err) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) {
         *err = "hipGetDevice failed";
-        return nullptr;
+        return {};
     }
     std::lock_guard<std::mutex> g(md.mu);
     auto it = md.spec.find(dev);
-    if (it != md.spec.end()) return it->second.second;
+    if (it != md.spec.end()) return it->second;
     std::vector<char> code;
-    if (!rtc_code(ode_spec_source(md.m), &code, err)) return nullptr;
-    hipModule_t mod = nullptr;
-    hipError_t e = hipModuleLoadData(&mod, code.data());
+    if (!rtc_code(ode_spec_source(md.m), &code, err)) return {};
+    lik_ode_t_::Spec s;
+    hipError_t e = hipModuleLoadData(&s.mod, code.data());
     if (e != hipSuccess) {
         *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e);
-        return nullptr;
+        return {};
     }
-    hipFunction_t fn = nullptr;
-    e = hipModuleGetFunction(&fn, mod, "lik_ode_spec");
+    e = hipModuleGetFunction(&s.fn, s.mod, "lik_ode_spec");
+    if (e == hipSuccess && ode_group_lanes(md.m))
+        e = hipModuleGetFunction(&s.group, s.mod, "lik_ode_group");
     if (e != hipSuccess) {
         *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e);
-        (void)hipModuleUnload(mod);
-        return nullptr;
+        (void)hipModuleUnload(s.mod);
+        return {};
     }
-    md.spec[dev] = {mod, fn};
-    return fn;
+    md.spec[dev] = s;
+    return s;
 }
 
 bool valid_param(int p, int V) { return p >= 0 && p < V; }
@@ -312,23 +404,47 @@ void model_args(const lik_ode_t_ &md, OdeArgs *a) {
     for (int k = 0; k < 5; ++k) a->fret[k] = md.m.fret_param[k];
 }
 
-// The specialised kernel when asked for (or by default, where it compiles).
-int pick_kernel(lik_ode_t_ &md, int32_t kernel, hipFunction_t *spec) {
-    *spec = nullptr;
+// The kernel of a call: the specialised ones when asked for (or by default,
+// where they compile), the group kernel for small populations.
+struct OdeLaunch {
+    hipFunction_t spec = nullptr;  // null: the generic kernel
+    unsigned lds = 0;
+    unsigned pairs = 64;           // (theta, trajectory) pairs per workgroup
+};
+
+// Up to this many pairs the group kernel is used: with one lane per pair they
+// leave SIMDs without a wavefront (65,536 lanes fill each with one).  ERK
+// batches, one lane per pair / groups of 16: 200 rate vectors (1,200 pairs)
+// 12.1 / 4.6 ms, 2,730 (16,380) 13.1 / 6.7 ms; from there the groups' time
+// grows by 0.22 ms per 1,000 pairs, the other's stays near 15 ms up to 50,000.
+constexpr size_t kOdeGroupPairs = 49152;
+
+int pick_kernel(lik_ode_t_ &md, int32_t kernel, size_t F, OdeLaunch *out) {
+    *out = OdeLaunch{};
     if (kernel == LIK_KERNEL_GENERIC) return LIK_OK;
     std::string msg;
-    *spec = ode_spec_kernel(md, &msg);
-    if (!*spec && kernel == LIK_KERNEL_SPECIALIZED)
+    const lik_ode_t_::Spec s = ode_spec_kernel(md, &msg);
+    if (!s.fn && kernel == LIK_KERNEL_SPECIALIZED)
         return fail(LIK_EDEVICE, "specialised ODE kernel unavailable: " + msg);
+    if (!s.fn) return LIK_OK;
+    if (s.group && F <= kOdeGroupPairs) {
+        out->spec = s.group;
+        out->lds = (unsigned)ode_group_lds(md.m);
+        out->pairs = (unsigned)(64 / ode_group_lanes(md.m));
+    } else {
+        out->spec = s.fn;
+        out->lds = (unsigned)ode_par_lds(md.m.n_params);
+    }
     return LIK_OK;
 }
 
 // Enqueues on s: the trajectory order (and the zeroed pair counter), the
 // solver over every pair, and the per-theta sums.  Every pointer in a is a
 // device pointer.
-int ode_enqueue(const OdeArgs &a, hipFunction_t spec, double *loglik, int32_t *status,
+int ode_enqueue(const OdeArgs &a, const OdeLaunch &k, double *loglik, int32_t *status,
                 hipStream_t s) {
-    const int U = a.U, V = a.V, M = a.M, n_theta = a.n_theta;
+    const int U = a.U, M = a.M, n_theta = a.n_theta;
+    const hipFunction_t spec = k.spec;
     const size_t F = (size_t)n_theta * M;
     hipLaunchKernelGGL(k_ode_order, dim3((unsigned)((M + 255) / 256)), dim3(256), 0, s,
                        a.obs_offsets, a.in_offsets, M, const_cast<int32_t *>(a.m_order), a.next);
@@ -336,10 +452,10 @@ int ode_enqueue(const OdeArgs &a, hipFunction_t spec, double *loglik, int32_t *s
     if (e != hipSuccess) return hip_fail(e, "ode order launch");
     // every lane takes pairs until none is left: as many workgroups as can
     // be resident at once (more would only find the counter spent)
-    const unsigned lds = spec ? (unsigned)ode_par_lds(V) : 0u;
+    const unsigned lds = k.lds;
     const void *gen = U <= 4 ? (const void *)k_ode<4> : U <= 8 ? (const void *)k_ode<8>
                     : U <= 16 ? (const void *)k_ode<16> : (const void *)k_ode<32>;
-    unsigned blocks = (unsigned)((F + 63) / 64);
+    unsigned blocks = (unsigned)((F + k.pairs - 1) / k.pairs);
     int per_cu = 0, cus = 0, dev_id = 0;
     const hipError_t eo = spec ? hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, spec,
                                                                                     64, lds)
@@ -414,7 +530,7 @@ int lik_ode_precompile(lik_ode_t model) {
 
 int lik_ode_destroy(lik_ode_t model) {
     if (model) {
-        for (auto &kv : model->spec) (void)hipModuleUnload(kv.second.first);
+        for (auto &kv : model->spec) (void)hipModuleUnload(kv.second.mod);
         for (auto &kv : model->dev) (void)hipFree(kv.second);
     }
     delete model;
@@ -454,8 +570,8 @@ int lik_ode_eval(lik_ode_t model, int32_t n_theta, const double *theta, const li
                     return fail(LIK_EINVAL, "input breakpoints must be finite and increase strictly");
             }
     }
-    hipFunction_t spec = nullptr;
-    if ((rc = pick_kernel(*model, kernel, &spec))) return rc;
+    OdeLaunch spec;
+    if ((rc = pick_kernel(*model, kernel, (size_t)n_theta * M, &spec))) return rc;
     OdeArgs a;
     memset(&a, 0, sizeof(a));
     if ((rc = model_on_device(*model, &a.terms, &a.x0_param))) return rc;
@@ -549,8 +665,8 @@ int lik_ode_eval_device(lik_ode_t model, int32_t n_theta, const double *theta,
     const size_t F = (size_t)n_theta * M;
     if (!workspace || workspace_bytes < lik_ode_workspace_size(model, n_theta, M))
         return fail(LIK_EINVAL, "workspace too small (see lik_ode_workspace_size)");
-    hipFunction_t spec = nullptr;
-    if ((rc = pick_kernel(*model, kernel, &spec))) return rc;
+    OdeLaunch spec;
+    if ((rc = pick_kernel(*model, kernel, F, &spec))) return rc;
     OdeArgs a;
     memset(&a, 0, sizeof(a));
     if ((rc = model_on_device(*model, &a.terms, &a.x0_param))) return rc;
