@@ -65,8 +65,8 @@ int32_t lik::split_goal(size_t slots, size_t chunks) {
 int32_t lik::flow_spare(int64_t intervals, int h_max, int64_t items_max) {
     const int64_t least = kPropBlock >> kSplitMax;  // particles of the smallest item
     const int64_t most = intervals * ((h_max + least - 1) / least);
-    // an empty wavefront costs its dispatch: bounded
-    return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, 1 << 18));
+    // an empty wavefront costs its dispatch, 0.25 ns: bounded
+    return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, 1 << 20));
 }
 
 namespace {

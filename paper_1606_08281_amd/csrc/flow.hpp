@@ -29,8 +29,8 @@
 // left times long items) would set the end of the run.  So the item ring is
 // kept short: a filter that is not urgent and finds `backlog` items already
 // waiting is parked (its id goes to a second ring) instead of appending its
-// items; every wavefront that finishes an item takes one parked filter and
-// appends its items while fewer than `backlog` wait.  Urgent filters always
+// items; every wavefront that finishes an interval takes parked filters and
+// appends their items while fewer than `backlog` wait.  Urgent filters always
 // append, and so wait only behind a short ring.  No deadlock: a filter is
 // parked only while items wait, and the last of them to finish un-parks.
 // At most one interval of items per filter is outstanding: its groups of 64,
@@ -62,13 +62,19 @@ __device__ __forceinline__ uint32_t ctl_load(const FlowArgs &fa, int w) {
     return __hip_atomic_load(&fa.ctl[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Progress of the launch: intervals finished (in items) and items claimed (a
+// wavefront that finishes its item leaves, and the next one claims).
+__device__ __forceinline__ uint32_t flow_progress(const FlowArgs &fa) {
+    return ctl_load(fa, kCtlProgress) + ctl_load(fa, kCtlHead + 64 * kRingItems);
+}
+
 // Gives up (sets the abort word, which every waiting wavefront then sees)
-// once no work item has finished for stall_ticks.  `seen` and `since` carry
+// once there has been no progress for stall_ticks.  `seen` and `since` carry
 // the wait's last progress count and its time.
 __device__ __forceinline__ bool flow_stalled(const FlowArgs &fa, uint32_t &seen,
                                              uint64_t &since) {
     if (ctl_load(fa, kCtlAbort) != 0u) return true;
-    const uint32_t prog = ctl_load(fa, kCtlProgress);
+    const uint32_t prog = flow_progress(fa);
     const uint64_t now = wall_clock64();
     if (prog != seen) {
         seen = prog;
@@ -89,14 +95,18 @@ __device__ __forceinline__ uint64_t *ring_slot(const FlowArgs &fa, int r, uint32
 // every filter is done.
 __device__ __forceinline__ bool ring_wait(const FlowArgs &fa, int r, uint32_t pos, uint32_t want,
                                           uint64_t *entry, bool until_done) {
-    uint64_t since = wall_clock64();
-    uint32_t seen = ctl_load(fa, kCtlProgress);
-    for (;;) {
+    uint64_t since = 0;
+    uint32_t seen = 0;
+    for (bool first = true;; first = false) {
         const uint64_t v =
             __hip_atomic_load(ring_slot(fa, r, pos), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if ((uint32_t)(v >> 32) == want) {
             *entry = v;
             return true;
+        }
+        if (first) {
+            since = wall_clock64();
+            seen = flow_progress(fa);
         }
         if (until_done && (int)ctl_load(fa, kCtlFinished) >= fa.n_slots) return false;
         if (flow_stalled(fa, seen, since)) return false;
@@ -205,17 +215,20 @@ __device__ __forceinline__ int settle_spare(const FlowArgs &fa, int code, int H,
 }
 
 // A filter's interval (item code `code`, expected events c, interval t) is
-// over: its share of the split items and of the weights.  One lane only.
+// over: its items (counted here once, not one by one: every finished item
+// adding to one word held 512 telegraph rate vectors in FP32-mixed to 12,500
+// items per ms), its share of the split ones and of the weights.  One lane only.
 __device__ __forceinline__ uint64_t leave_interval(const FlowArgs &fa, const FilterDesc &d,
                                                    int code, uint32_t c, int t) {
-    const int extra = code_items(code, d.H) - (d.Hp >> 6);
+    const int n_items = code_items(code, d.H), extra = n_items - (d.Hp >> 6);
     if (extra > 0) ctl_add(fa, kCtlExtra, (uint32_t)-extra);
+    ctl_add(fa, kCtlProgress, (uint32_t)n_items);
     return flow_weight(d, c, t);
 }
 
 // While the item ring is short and filters are parked, takes one parked
 // filter and writes its items; false if it took none.  Called by every
-// wavefront that finishes an item, and by the wavefront first in line for
+// wavefront that finishes an interval, and by the wavefront first in line for
 // the next item while it waits, so that parked filters move as soon as
 // there is room.
 __device__ __forceinline__ bool flow_unpark(const EngineArgs &e, const FlowArgs &fa, int lane) {
@@ -238,11 +251,11 @@ __device__ __forceinline__ bool flow_unpark(const EngineArgs &e, const FlowArgs 
     if (f < 0) return false;
     // acquire the parked filter's state (its items' takers acquire it themselves)
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    emit_items(e, fa, f, (int)e.pool[f], lane);
+    emit_items(e, fa, f, (int)e.pool[f] & 63, lane);
     return true;
 }
 
-// After an item: takes parked filters (at most kUnparkPerItem) while the
+// After an interval: takes parked filters (at most kUnparkPerItem) while the
 // item ring is short.
 constexpr int kUnparkPerItem = 4;
 __device__ __forceinline__ void flow_unpark_some(const EngineArgs &e, const FlowArgs &fa,
@@ -255,23 +268,41 @@ __device__ __forceinline__ void flow_unpark_some(const EngineArgs &e, const Flow
 // entry in *entry; 2 when this wavefront is first in line (no producer has
 // reserved pos yet) and filters are parked -- the caller un-parks one and
 // waits again; 0 once every filter is done or the flow has given up.
+// Thousands of wavefronts may wait here while a few work, and the control
+// words they would read are the ones every hand-off goes through: a waiting
+// wavefront reads its own ring slot, and the control words every eighth time;
+// one far from its turn sleeps longer and reads one of them.
 __device__ __forceinline__ int item_wait(const FlowArgs &fa, uint32_t pos, uint64_t *entry) {
-    uint64_t since = wall_clock64();
-    uint32_t seen = ctl_load(fa, kCtlProgress);
-    for (;;) {
+    constexpr uint32_t kFar = 256;  // positions beyond the last item written
+    uint64_t since = 0;
+    uint32_t seen = 0;
+    bool far = false;
+    for (uint32_t n = 0;; ++n) {
         const uint64_t v = __hip_atomic_load(ring_slot(fa, kRingItems, pos), __ATOMIC_RELAXED,
                                              __HIP_MEMORY_SCOPE_AGENT);
         if ((uint32_t)(v >> 32) == pos + 1u) {
             *entry = v;
             return 1;
         }
-        if (ctl_load(fa, kCtlTail + 64 * kRingItems) == pos &&
-            (int32_t)(ctl_load(fa, kCtlTail + 64 * kRingParked) -
-                      ctl_load(fa, kCtlHead + 64 * kRingParked)) > 0)
-            return 2;
-        if ((int)ctl_load(fa, kCtlFinished) >= fa.n_slots) return 0;
-        if (flow_stalled(fa, seen, since)) return 0;
-        __builtin_amdgcn_s_sleep(8);
+        if (n == 0) {
+            since = wall_clock64();
+            seen = flow_progress(fa);
+        }
+        if ((n & 7u) == 0u || far) {
+            if ((int)ctl_load(fa, kCtlFinished) >= fa.n_slots) return 0;
+        }
+        if ((n & 7u) == 0u) {
+            const uint32_t tail = ctl_load(fa, kCtlTail + 64 * kRingItems);
+            if (tail == pos && (int32_t)(ctl_load(fa, kCtlTail + 64 * kRingParked) -
+                                         ctl_load(fa, kCtlHead + 64 * kRingParked)) > 0)
+                return 2;
+            if (flow_stalled(fa, seen, since)) return 0;
+            far = (int32_t)(pos - tail) > (int32_t)kFar;
+        }
+        if (far)
+            __builtin_amdgcn_s_sleep(100);
+        else
+            __builtin_amdgcn_s_sleep(32);
     }
 }
 
@@ -534,15 +565,19 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
     __syncthreads();  // the weighing's state (tcur, ancestors) from every lane
     // lane 0 wrote tcur: its reading decides, for every lane
     const int H = e.desc[f].H;
-    int code = 0;
+    int code = 0, prio = 0;
     if (lane == 0) {
         const FilterDesc &d = e.desc[f];
         const int t = e.tcur[f], nchunk = d.Hp >> 6;
-        const uint64_t was = leave_interval(fa, d, e.pool[f], e.cost[f], t - 1);
+        const uint64_t was = leave_interval(fa, d, e.pool[f] & 63, e.cost[f], t - 1);
         const uint64_t w = flow_weight(d, cost, t);
         const uint64_t sum = add_weight(fa, w - was);
         code = settle_spare(fa, item_code(e, f, cost, fa.g_par, flow_goal(fa, w, sum, nchunk)), H,
                             nchunk);
+        // wavefront priority for the longest chains left (2 and 4 times the
+        // average): 256 Lac-Gfp rate vectors 655 -> 598 ms
+        const double chain = (double)w * (double)(fa.n_slots - (int)ctl_load(fa, kCtlFinished));
+        prio = chain >= 4.0 * (double)sum ? 3 : chain >= 2.0 * (double)sum ? 1 : 0;
     }
     code = __builtin_amdgcn_readfirstlane(code);
     const int n_items = code_items(code, H);
@@ -550,7 +585,7 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
         (int)(!flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
     if (lane == 0) {
         store_global(e.cost, (uint32_t)f, cost);
-        store_global(e.pool, (uint32_t)f, (uint8_t)code);
+        store_global(e.pool, (uint32_t)f, (uint8_t)((prio << 6) | code));
         __hip_atomic_store(&fa.remaining[f], (uint32_t)n_items, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
@@ -590,8 +625,12 @@ template <class RunItem>
 __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArgs &fa,
                                               uint32_t *lds, RunItem &&run) {
     __shared__ double logy[LIK_MAX_OBSERVED];
-    // the wavefronts beyond the batch's last item start after it is done
-    if ((int)__builtin_amdgcn_readfirstlane(ctl_load(fa, kCtlFinished)) >= fa.n_slots) return;
+    // the wavefronts beyond the batch's last item start after it is done (a
+    // cached reading: one that is out of date waits for an item and finds out)
+    if ((int)__builtin_amdgcn_readfirstlane(
+            __hip_atomic_load(&fa.ctl[kCtlFinished], __ATOMIC_RELAXED,
+                              __HIP_MEMORY_SCOPE_WORKGROUP)) >= fa.n_slots)
+        return;
     uint64_t ent = 0;
     uint32_t pos = 0;
     if (lane_id() == 0)
@@ -625,17 +664,11 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
     // would otherwise stay in scalar registers through the event loop).
     const EngineArgs &ec = reload_engine_args();
     uint32_t left = 0;
-    if (lane_id() == 0) {
+    if (lane_id() == 0)
         left = __hip_atomic_fetch_sub(&fa.remaining[f], 1u, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
-        __hip_atomic_fetch_add(&fa.ctl[kCtlProgress], 1u, __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-    }
     left = __builtin_amdgcn_readfirstlane(left);
-    if (left != 1u) {
-        flow_unpark_some(ec, fa, lane_id());
-        return;
-    }
+    if (left != 1u) return;
     // the last item of the interval: weigh the filter with every item's results
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     uint32_t cost = 0;
@@ -644,7 +677,7 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
         flow_unpark_some(ec, fa, lane_id());
     } else {
         if (lane_id() == 0) {
-            add_weight(fa, 0 - leave_interval(fa, ec.desc[f], ec.pool[f], ec.cost[f],
+            add_weight(fa, 0 - leave_interval(fa, ec.desc[f], ec.pool[f] & 63, ec.cost[f],
                                               ec.tcur[f] - 1));
             if (ec.fdone) store_global(ec.fdone, (uint32_t)f, (uint64_t)wall_clock64());
             __hip_atomic_fetch_add(&fa.ctl[kCtlFinished], 1u, __ATOMIC_RELAXED,

@@ -161,7 +161,7 @@ enum : int {
     kCtlTail = 32,        // + 64 r: next position of ring r an entry is written to
     kCtlFinished = 128,   // slots that need no further interval
     kCtlAbort = 160,      // nonzero: a wavefront saw no progress for stall_ticks
-    kCtlProgress = 192,   // work items finished
+    kCtlProgress = 192,   // work items of finished intervals
     kCtlSeedItems = 224,  // items of the first interval placed in the item ring
     kCtlSpare = 240,      // wavefronts of the launch no item needs so far (signed)
     kCtlExtra = 241,      // items outstanding beyond one per group of 64 (signed)

