@@ -171,11 +171,19 @@ __device__ __forceinline__ void emit_items(const EngineArgs &e, const FlowArgs &
 // its particles (c: of its whole next interval) times its intervals left, from
 // interval t on -- the length of its chain.
 __device__ __forceinline__ uint64_t flow_weight(const FilterDesc &d, uint32_t c, int t) {
-    return (uint64_t)min(c / (uint32_t)d.H, 1u << 20) * (uint64_t)(d.T - t);
+    return min((uint64_t)(c / (uint32_t)d.H) * (uint64_t)(d.T - t), (uint64_t)1 << 30);
 }
-__device__ __forceinline__ uint64_t add_weight(const FlowArgs &fa, uint64_t by) {  // returns the sum
-    return by + __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(&fa.ctl[kCtlWeight]), by,
+// Adds to one of the two sums over the unfinished filters; returns the sum.
+__device__ __forceinline__ uint64_t add_weight(const FlowArgs &fa, int word, uint64_t by) {
+    return by + __hip_atomic_fetch_add(reinterpret_cast<uint64_t *>(&fa.ctl[word]), by,
                                        __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// A filter is critical when its chain of events alone takes about as long as
+// everything left, spread over the GPU's wavefronts (waves: one per SIMD):
+// the launch then ends with it, whatever the others do.
+__device__ __forceinline__ bool flow_critical(const FlowArgs &fa, uint64_t w, uint64_t work) {
+    return (uint64_t)fa.split_waves * w >= work;
 }
 __device__ __forceinline__ uint32_t ctl_add(const FlowArgs &fa, int w, uint32_t by) {
     return __hip_atomic_fetch_add(&fa.ctl[w], by, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -185,15 +193,18 @@ __device__ __forceinline__ uint32_t ctl_add(const FlowArgs &fa, int w, uint32_t 
 // share, by weight, of split_waves, as far as the items running now leave
 // room (none while items wait).  A batch that keeps the GPU busy is not split:
 // an item of 32 particles issues 1.3 times the instructions of its half of 64.
+// A critical filter is, into items of 16, from the start on: 512 uneven requests
+// 218 -> 208 ms, 256 Lac-Gfp rate vectors 598 -> 569 ms (means of three seeds).
 __device__ __forceinline__ int flow_goal(const FlowArgs &fa, uint64_t w, uint64_t sum,
-                                         int nchunk) {
+                                         int nchunk, bool critical) {
+    const int least = critical ? 4 * nchunk : 0;
     const uint32_t head = ctl_load(fa, kCtlHead + 64 * kRingItems);
     const uint32_t tail = ctl_load(fa, kCtlTail + 64 * kRingItems);
     const uint32_t done = ctl_load(fa, kCtlProgress);
-    if ((int32_t)(tail - head) > 0 || sum == 0) return 0;
+    if ((int32_t)(tail - head) > 0 || sum == 0) return least;
     const int room = (int)fa.split_waves - (int)(tail - done);
-    if (room <= 0) return 0;
-    return min((int)((double)fa.split_waves * ((double)w / (double)sum)), nchunk + room);
+    if (room <= 0) return least;
+    return max(least, min((int)((double)fa.split_waves * ((double)w / (double)sum)), nchunk + room));
 }
 
 // The launch has one wavefront per group of 64 particles of every interval
@@ -565,24 +576,27 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
     __syncthreads();  // the weighing's state (tcur, ancestors) from every lane
     // lane 0 wrote tcur: its reading decides, for every lane
     const int H = e.desc[f].H;
-    int code = 0, prio = 0;
+    int code = 0, prio = 0, critical = 0;
     if (lane == 0) {
         const FilterDesc &d = e.desc[f];
         const int t = e.tcur[f], nchunk = d.Hp >> 6;
         const uint64_t was = leave_interval(fa, d, e.pool[f] & 63, e.cost[f], t - 1);
         const uint64_t w = flow_weight(d, cost, t);
-        const uint64_t sum = add_weight(fa, w - was);
-        code = settle_spare(fa, item_code(e, f, cost, fa.g_par, flow_goal(fa, w, sum, nchunk)), H,
-                            nchunk);
+        const uint64_t sum = add_weight(fa, kCtlWeight, w - was);
+        const uint64_t work = add_weight(fa, kCtlWork, (w - was) * (uint64_t)nchunk);
+        critical = flow_critical(fa, w, work);
+        code = settle_spare(
+            fa, item_code(e, f, cost, fa.g_par, flow_goal(fa, w, sum, nchunk, critical != 0)), H,
+            nchunk);
         // wavefront priority for the longest chains left (2 and 4 times the
         // average): 256 Lac-Gfp rate vectors 655 -> 598 ms
         const double chain = (double)w * (double)(fa.n_slots - (int)ctl_load(fa, kCtlFinished));
-        prio = chain >= 4.0 * (double)sum ? 3 : chain >= 2.0 * (double)sum ? 1 : 0;
+        prio = critical || chain >= 4.0 * (double)sum ? 3 : chain >= 2.0 * (double)sum ? 1 : 0;
     }
     code = __builtin_amdgcn_readfirstlane(code);
     const int n_items = code_items(code, H);
     const int park = __builtin_amdgcn_readfirstlane(
-        (int)(!flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
+        (int)(!critical && !flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
     if (lane == 0) {
         store_global(e.cost, (uint32_t)f, cost);
         store_global(e.pool, (uint32_t)f, (uint8_t)((prio << 6) | code));
@@ -677,8 +691,10 @@ __device__ __forceinline__ void flow_run_with(const EngineArgs &e, const FlowArg
         flow_unpark_some(ec, fa, lane_id());
     } else {
         if (lane_id() == 0) {
-            add_weight(fa, 0 - leave_interval(fa, ec.desc[f], ec.pool[f] & 63, ec.cost[f],
-                                              ec.tcur[f] - 1));
+            const uint64_t was = leave_interval(fa, ec.desc[f], ec.pool[f] & 63, ec.cost[f],
+                                                ec.tcur[f] - 1);
+            add_weight(fa, kCtlWeight, 0 - was);
+            add_weight(fa, kCtlWork, 0 - was * (uint64_t)(ec.desc[f].Hp >> 6));
             if (ec.fdone) store_global(ec.fdone, (uint32_t)f, (uint64_t)wall_clock64());
             __hip_atomic_fetch_add(&fa.ctl[kCtlFinished], 1u, __ATOMIC_RELAXED,
                                    __HIP_MEMORY_SCOPE_AGENT);

@@ -340,7 +340,9 @@ __global__ void k_flow_seed(EngineArgs e, FlowArgs fa, int pass) {
     const bool urgent = flow_urgent(e, fa, f, e.cost[f], code < kSplitCode ? code + 1 : 1);
     if (urgent != (pass == 0)) return;
     code = settle_spare(fa, code, e.desc[f].H, e.desc[f].Hp >> 6);
-    add_weight(fa, flow_weight(e.desc[f], e.cost[f], 0));
+    const uint64_t w = flow_weight(e.desc[f], e.cost[f], 0);
+    add_weight(fa, kCtlWeight, w);
+    add_weight(fa, kCtlWork, w * (uint64_t)(e.desc[f].Hp >> 6));
     const int n_items = code_items(code, e.desc[f].H);
     e.pool[f] = (uint8_t)code;
     fa.remaining[f] = (uint32_t)n_items;

@@ -166,6 +166,7 @@ enum : int {
     kCtlSpare = 240,      // wavefronts of the launch no item needs so far (signed)
     kCtlExtra = 241,      // items outstanding beyond one per group of 64 (signed)
     kCtlWeight = 242,     // 64 bits: flow_weight summed over the filters not finished
+    kCtlWork = 244,       // 64 bits: flow_weight times groups of 64, summed likewise
     kCtlArgs = 256,       // a copy of the launch's FlowArgs (16 words)
     kCtlWords = 272
 };
