@@ -57,9 +57,8 @@ uint32_t lik::compute_units() {
 
 uint32_t lik::split_waves() { return std::min(compute_units() * kSplitWavesPerCu, 4096u); }
 
-int32_t lik::split_goal(size_t slots, size_t chunks) {
-    if (slots == 0 || chunks >= kSplitChunks) return 0;
-    return (int32_t)(split_waves() / slots);
+int32_t lik::split_goal(size_t slots) {
+    return slots == 0 ? 0 : (int32_t)(split_waves() / slots);
 }
 
 int32_t lik::flow_spare(int64_t intervals, int h_max, int64_t items_max) {
@@ -404,7 +403,7 @@ size_t lik_workspace_size(lik_network_t net, int32_t n_theta, int32_t n_traj,
     b += align256(item_list_capacity(F * (Hp / 64)) * 4);  // items
     b += align256(kMaxGroups * 4);            // item_count
     b += align256(kMaxGroups * 4);            // item_cursor
-    b += 2 * align256(kMaxGroups * kCostKeys * 4) + align256(2 * 4);  // ordering passes
+    b += 2 * align256(kMaxGroups * kCostKeys * 4) + align256(kOrderCtlWords * 4);  // ordering passes
     b += align256((size_t)flow_ring_capacity(F, Hp / 64) * 8 * kFlowRings);  // flow rings
     b += align256(F * 4);                     // flow: items left per slot
     b += align256(kCtlWords * 4);             // flow: control words
@@ -457,7 +456,7 @@ EngineLayout carve_engine(char *p, size_t slots, size_t items, size_t state_byte
     L.e.item_cursor = (uint32_t *)take(kMaxGroups * 4);
     L.e.order_count = (uint32_t *)take(kMaxGroups * kCostKeys * 4);
     L.e.order_pos = (uint32_t *)take(kMaxGroups * kCostKeys * 4);
-    L.e.order_ctl = (uint32_t *)take(2 * 4);
+    L.e.order_ctl = (uint32_t *)take(kOrderCtlWords * 4);
     memset(&L.fa, 0, sizeof(L.fa));
     L.fa.ring = (uint64_t *)take((size_t)ring_capacity * 8 * kFlowRings);
     L.fa.remaining = (uint32_t *)take(slots * 4);
@@ -642,8 +641,11 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
                             : specialized_kernel(*net, precision, &err, kSpecPersistent);
 
     if (!G.persistent) {  // the per-interval schedule's splitting
-        L.e.split_goal = split_goal(F, F * nchunk);
-        G.max_items = (unsigned)(F * (size_t)std::max(nchunk, L.e.split_goal));
+        if (F * nchunk < kSplitChunks) {  // (the item list has room)
+            L.e.split_goal = split_goal(F);
+            L.e.split_budget = (int32_t)split_waves();
+            G.max_items += split_waves();
+        }
     }
 
     // flow schedule: its kernel and one wavefront per work item the batch can
@@ -666,6 +668,7 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
         flow = per_cu >= kFlowMinWavesPerCu;
     }
     if (flow) {
+        L.e.split_budget = 0;
         L.fa.split_waves = split_waves();
         L.fa.spare = flow_spare((int64_t)n_theta * total, H, (int64_t)items_max);
         flow_waves = (unsigned)std::max<size_t>(items_max + (size_t)L.fa.spare, 1);
@@ -742,7 +745,9 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
             e = launch_order_reset(L.e, st);
             if (e != hipSuccess) return hip_fail(e, "order reset launch");
             for (int t = 0; t < t_max; ++t) {
-                e = engine_iteration(L.e, &G, 1, st, timed);
+                EngineArgs it = L.e;
+                it.order_parity = t & 1;
+                e = engine_iteration(it, &G, 1, st, timed);
                 if (e != hipSuccess) return hip_fail(e, "iteration launch");
             }
         }

@@ -110,9 +110,8 @@ int hip_fail(hipError_t e, const char *where);
 uint32_t compute_units();  // of the current device
 // Wavefronts that batches too small to fill the device are spread over.
 uint32_t split_waves();
-// Items per slot for the per-interval schedule: `slots` slots with `chunks`
-// groups of 64 particles in all (0: no splitting).
-int32_t split_goal(size_t slots, size_t chunks);
+// An even share of those items per slot for the per-interval schedule (0: none).
+int32_t split_goal(size_t slots);
 // Wavefronts a flow launch takes beyond one per group of 64 particles, so that
 // every interval can be split: `intervals` filter-intervals of at most h_max
 // particles with items_max groups in all.

@@ -39,6 +39,16 @@ namespace lik {
 // round to infinity, and infinity times a zero mass-action factor is NaN) --
 // mark every slot of that theta BAD_THETA before any simulation.
 // ---------------------------------------------------------------------------
+// An estimate of a slot's events per particle into the sum of the iteration of
+// parity p (only where iterations split by it).
+__device__ __forceinline__ uint64_t *order_sum(const EngineArgs &e, int p) {
+    return reinterpret_cast<uint64_t *>(&e.order_ctl[4 + 2 * p]);
+}
+__device__ __forceinline__ void add_order_sum(const EngineArgs &e, int p, uint32_t per) {
+    if (e.split_budget > 0)
+        atomicAdd(reinterpret_cast<unsigned long long *>(order_sum(e, p)), (unsigned long long)per);
+}
+
 // Filter k of request r (theta k / M against trajectory k % M) into its slot.
 __device__ __forceinline__ void admit_one(FilterDesc *desc, const EngineArgs &e,
                                           const RequestArgs &r, int k) {
@@ -112,7 +122,10 @@ __device__ __forceinline__ void admit_one(FilterDesc *desc, const EngineArgs &e,
         }
     }
     const double expect = (double)r.H * a0 * (d.t_obs[0] - d.t0);
-    e.cost[f] = !(expect > 0.0) ? 0u : expect >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)expect;
+    const uint32_t c =
+        !(expect > 0.0) ? 0u : expect >= 4294967295.0 ? 0xFFFFFFFFu : (uint32_t)expect;
+    e.cost[f] = c;
+    if (!bad) add_order_sum(e, e.order_parity, c / (uint32_t)r.H);
 }
 
 __global__ void k_admit(FilterDesc *desc, EngineArgs e, RequestArgs r) {
@@ -202,6 +215,24 @@ __device__ __forceinline__ int item_key(uint32_t c, int H, int code) {
     return duration_key((uint64_t)(c / (uint32_t)H) * (uint64_t)(code < kSplitCode ? code + 1 : 1));
 }
 
+// Item code of slot f in this iteration: an iteration lasts as long as its
+// longest item, so the slots expected to need the most events are cut finest --
+// each gets its share, by expected events per particle, of split_budget items
+// (an even share before any estimate).  Items beyond the budget, which the item
+// list and the launch have no room for, are not split.
+__device__ __forceinline__ int order_code(const EngineArgs &e, int f, uint32_t c) {
+    if (e.split_budget <= 0) return pool_size(e, f, c, order_gpar(e)) - 1;
+    const int H = e.desc[f].H;
+    const uint64_t sum = *order_sum(e, e.order_parity);
+    const int goal = sum == 0 ? e.split_goal
+                              : (int)((double)e.split_budget * (double)(c / (uint32_t)H) / (double)sum);
+    const int code = item_code(e, f, c, order_gpar(e), goal);
+    const int need = code_items(code, H) - (e.desc[f].Hp >> 6);
+    if (need > 0 && (int)atomicAdd(&e.order_ctl[2], (uint32_t)need) + need > e.split_budget)
+        return 0;
+    return code;
+}
+
 __global__ __launch_bounds__(kOrderBlock) void k_order_count(EngineArgs e) {
     __shared__ uint32_t hist[kMaxGroups * kCostKeys];
     __shared__ uint32_t max_per;
@@ -211,7 +242,8 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_count(EngineArgs e) {
     const int f = e.f_lo + (int)(blockIdx.x * kOrderBlock + threadIdx.x);
     if (f < e.f_hi && slot_active(e, f)) {
         const uint32_t c = e.cost[f];
-        const int code = item_code(e, f, c, order_gpar(e), e.split_goal);
+        const int code = order_code(e, f, c);
+        e.pool[f] = (uint8_t)code;
         const int key = item_key(c, e.desc[f].H, code);
         atomicAdd(&hist[e.desc[f].group * kCostKeys + key],
                   (uint32_t)code_items(code, e.desc[f].H));
@@ -246,6 +278,8 @@ __global__ __launch_bounds__(64 * kMaxGroups) void k_order_scan(EngineArgs e) {
     if (threadIdx.x == 0) {
         e.order_ctl[1] = e.order_ctl[0];
         e.order_ctl[0] = 0u;
+        e.order_ctl[2] = 0u;
+        *order_sum(e, e.order_parity ^ 1) = 0ull;  // the next iteration's
     }
 }
 
@@ -262,7 +296,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
     int code = 0, gk = 0;
     if (on) {
         c = e.cost[f];
-        code = item_code(e, f, c, order_gpar(e), e.split_goal);  // as in the counting pass
+        code = (int)e.pool[f];  // the counting pass's
         gk = e.desc[f].group * kCostKeys + item_key(c, e.desc[f].H, code);
         n_items = (uint32_t)code_items(code, e.desc[f].H);
         local = atomicAdd(&lcount[gk], n_items);
@@ -288,7 +322,7 @@ __global__ __launch_bounds__(kOrderBlock) void k_order_place(EngineArgs e) {
 
 __global__ void k_order_reset(EngineArgs e) {
     for (int k = threadIdx.x; k < kMaxGroups * kCostKeys; k += blockDim.x) e.order_count[k] = 0u;
-    if (threadIdx.x < 2) e.order_ctl[threadIdx.x] = 0u;
+    if (threadIdx.x < kOrderCtlWords) e.order_ctl[threadIdx.x] = 0u;
 }
 
 // ---------------------------------------------------------------------------
@@ -548,7 +582,9 @@ __global__ __launch_bounds__(kWeighBlock) void k_weigh(EngineArgs e) {
     if (tid == 0) {
         double tot = 0.0;
         for (int w = 0; w < kWeighBlock / 64; ++w) tot += red[w];
-        e.cost[f] = cost_estimate(d, t, tot);
+        const uint32_t c = cost_estimate(d, t, tot);
+        e.cost[f] = c;
+        add_order_sum(e, e.order_parity ^ 1, c / (uint32_t)H);
     }
 }
 

@@ -113,6 +113,8 @@ struct FilterDesc {
     int32_t obs_species[LIK_MAX_OBSERVED];
 };
 
+constexpr int kOrderCtlWords = 8;
+
 // Everything an iteration's kernels need: the filter table, its mutable
 // state and the grouped work items.
 struct EngineArgs {
@@ -131,8 +133,12 @@ struct EngineArgs {
     uint32_t *order_count;    // [kMaxGroups * kCostKeys] items per (group, duration key);
                               // zero between iterations
     uint32_t *order_pos;      // [kMaxGroups * kCostKeys] next position of each (group, key)
-    uint32_t *order_ctl;      // [2]: most expected events per particle of any slot (zero
-                              // between iterations), and its copy for the placing pass
+    uint32_t *order_ctl;      // [kOrderCtlWords]: most expected events per particle of any
+                              // slot (zero between iterations), and its copy for the
+                              // placing pass; [2] split items beyond one per group of 64
+                              // (zeroed by the scan); [4 + 2 p] 64 bits: expected events
+                              // per particle summed over the slots of an iteration of
+                              // parity p (added when an estimate is made, before it)
     uint32_t pool_chunks;     // groups of 64 particles over the slots that may be active
     uint64_t *fdone;          // [slots] device wall clock when the slot's filter finished, or
                               // null (not recorded)
@@ -146,8 +152,12 @@ struct EngineArgs {
     uint32_t pool_min_items;  // work items an iteration keeps before pools grow
     int32_t h_max;            // most particles of any active slot (LDS of k_weigh)
     int32_t item_shift;       // bits of a work item's chunk number (item_shift_for)
+    int32_t order_parity;     // of this iteration, or (admission) of the next one
+    int32_t split_budget;     // per-interval schedule: items that splitting may add to an
+                              // iteration (0: no splitting)
     int32_t split_goal;       // per-interval schedule: items a slot is cut into, its groups of
-                              // 64 particles allowing (0: only by its pool size)
+                              // 64 particles allowing, while the iteration's sum of
+                              // expected events is not known (0: only by its pool size)
     uint32_t group_off[kMaxGroups];  // first item of each group
 };
 

@@ -123,10 +123,11 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     const size_t o_tcur = c.take((size_t)F * 4), o_fst = c.take((size_t)F * 4);
     const size_t o_ffl = c.take((size_t)F * 4), o_cost = c.take((size_t)F * 4);
     const size_t o_pool = c.take((size_t)F), o_fll = c.take((size_t)F * 8);
-    const size_t o_fev = c.take((size_t)F * 8), o_items = c.take(item_list_capacity((size_t)chunks) * 4);
+    const size_t o_fev = c.take((size_t)F * 8), o_items = c.take(((size_t)chunks + kMaxGroups * split_waves()) * 4);
     const size_t o_icount = c.take(kMaxGroups * 4), o_icur = c.take(kMaxGroups * 4);
     const size_t o_ocount = c.take(kMaxGroups * kCostKeys * 4);
-    const size_t o_opos = c.take(kMaxGroups * kCostKeys * 4), o_octl = c.take(2 * 4);
+    const size_t o_opos = c.take(kMaxGroups * kCostKeys * 4);
+    const size_t o_octl = c.take(kOrderCtlWords * 4);
     const size_t o_ring = c.take((size_t)ring_cap * 8 * kFlowRings);
     const size_t o_rem = c.take((size_t)F * 4), o_ctl = c.take(kCtlWords * 4);
     const size_t o_fdone = c.take((size_t)F * 8), o_start = c.take(8);
@@ -302,12 +303,13 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
         std::vector<int64_t> need(nets.size(), 0);
         for (int k = 0; k < n_req; ++k)
             need[(size_t)plan[(size_t)k].group] += plan[(size_t)k].F * (plan[(size_t)k].Hp / 64);
-        std::vector<int64_t> slots(nets.size(), 0);
-        for (int k = 0; k < n_req; ++k) slots[(size_t)plan[(size_t)k].group] += plan[(size_t)k].F;
-        if (!tu.persistent) e.split_goal = split_goal((size_t)F, (size_t)chunks);
+        if (!tu.persistent) {
+            e.split_goal = split_goal((size_t)F);
+            e.split_budget = (int32_t)split_waves();
+        }
         uint32_t off = 0;
         for (size_t g = 0; g < nets.size(); ++g) {
-            need[g] += slots[g] * e.split_goal;  // room for split items
+            need[g] += e.split_budget;  // room for split items
             GroupLaunch &G = groups[g];
             G.netargs = generic_netargs(*nets[g]);
             G.umax = nets[g]->umax;
@@ -364,8 +366,10 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
             if ((err = launch_flow_check(e, fa, s)) != hipSuccess) { rc = hip_fail(err, "flow check"); break; }
         } else {
             if ((err = launch_order_reset(e, s)) != hipSuccess) { rc = hip_fail(err, "order reset"); break; }
-            for (int t = 0; t < t_max && err == hipSuccess; ++t)
+            for (int t = 0; t < t_max && err == hipSuccess; ++t) {
+                e.order_parity = t & 1;
                 err = engine_iteration(e, groups, (int)nets.size(), s);
+            }
             if (err != hipSuccess) { rc = hip_fail(err, "iteration launch"); break; }
         }
         err = launch_finish_requests(e, (const ReqSpan *)(dev + o_spans), n_req,

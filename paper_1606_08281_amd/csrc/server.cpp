@@ -426,22 +426,21 @@ void worker_main(lik_server *S) {
         }
         // one iteration over every resident filter
         GroupLaunch launches[kMaxGroups];
-        unsigned need[kMaxGroups] = {0}, filters[kMaxGroups] = {0};
+        unsigned need[kMaxGroups] = {0};
         unsigned chunks = 0, running = 0;
         int32_t h_max = 1;
         for (auto &r : S->resident)
             if (r->iterations_left > 0) {
                 need[r->group] += (unsigned)(r->F() * (r->Hp / 64));
-                filters[r->group] += (unsigned)r->F();
                 chunks += (unsigned)(r->F() * (r->Hp / 64));
                 running += (unsigned)r->F();
                 h_max = std::max(h_max, r->H);
             }
         S->e.h_max = h_max;
-        S->e.split_goal = S->persistent ? 0 : split_goal(running, chunks);
+        S->e.split_goal = S->persistent ? 0 : split_goal(running);
         unsigned off = 0;
         for (int g = 0; g < kMaxGroups; ++g) {
-            need[g] += filters[g] * (unsigned)S->e.split_goal;  // room for split items
+            if (need[g]) need[g] += (unsigned)S->e.split_budget;  // room for split items
             launches[g] = S->groups[g].launch;
             launches[g].max_items = need[g];
             S->e.group_off[g] = off;
@@ -452,6 +451,7 @@ void worker_main(lik_server *S) {
         S->e.pool_chunks = chunks;  // groups of 64 particles of the slots still running
         if (engine_iteration(S->e, launches, kMaxGroups, S->stream) != hipSuccess)
             S->worker_error = "iteration launch failed";
+        S->e.order_parity ^= 1;  // admissions add their estimates to the next iteration's sum
         S->n_iterations += 1;
         for (auto &r : S->resident) {
             if (r->iterations_left <= 0) continue;
@@ -506,10 +506,10 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     const size_t slots = (size_t)o.max_filters;
     const size_t table = align256(slots * sizeof(FilterDesc)) + 4 * align256(slots * 4) +
                          align256(slots) +
-                         2 * align256(slots * 8) + align256((slots * 64 + split_waves()) * 4) +
+                         2 * align256(slots * 8) + align256((slots * 64 + kMaxGroups * split_waves()) * 4) +
                          2 * align256(kMaxGroups * 4) + align256(slots * 8) +
                          align256(slots * 4) + 2 * align256(kMaxGroups * kCostKeys * 4) +
-                         align256(2 * 4);
+                         align256(kOrderCtlWords * 4);
     hipError_t err = hipMalloc((void **)&S->dev_base, table + o.arena_bytes + 256);
     if (err != hipSuccess) return fail(LIK_ENOMEM, "device arena allocation failed");
     const size_t pinned_bytes = o.staging_bytes + slots * 12 + 512;
@@ -534,13 +534,13 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     S->e.pool = (uint8_t *)take(slots);
     S->e.fll = (double *)take(slots * 8);
     S->e.fevents = (uint64_t *)take(slots * 8);
-    S->e.items = (uint32_t *)take((slots * 64 + split_waves()) * 4);
+    S->e.items = (uint32_t *)take((slots * 64 + kMaxGroups * split_waves()) * 4);
     S->e.item_shift = item_shift_for(slots);
     S->e.item_count = (uint32_t *)take(kMaxGroups * 4);
     S->e.item_cursor = (uint32_t *)take(kMaxGroups * 4);
     S->e.order_count = (uint32_t *)take(kMaxGroups * kCostKeys * 4);
     S->e.order_pos = (uint32_t *)take(kMaxGroups * kCostKeys * 4);
-    S->e.order_ctl = (uint32_t *)take(2 * 4);
+    S->e.order_ctl = (uint32_t *)take(kOrderCtlWords * 4);
     S->dev_loglik = (double *)take(slots * 8);
     S->dev_status = (int32_t *)take(slots * 4);
     S->arena = p;
@@ -558,16 +558,18 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     S->e.priority = tu.priority;
     S->e.pool_min_items = (uint32_t)tu.items_per_cu * compute_units();
     S->persistent = tu.persistent != 0;
+    S->e.split_budget = S->persistent ? 0 : (int32_t)split_waves();
     S->pmem.init(o.staging_bytes, 256);
     // every slot starts inactive (stopped), so stale slots are never ordered
     std::vector<uint32_t> stopped(slots, kFlagStopped);
     // the ordering passes' counts start at zero (each iteration leaves them so)
-    std::vector<uint32_t> zeros(kMaxGroups * kCostKeys + 2, 0u);
+    std::vector<uint32_t> zeros(kMaxGroups * kCostKeys, 0u);
     if (hipStreamCreate(&S->stream) != hipSuccess ||
         hipMemcpy(S->e.fflags, stopped.data(), slots * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(S->e.order_count, zeros.data(), kMaxGroups * kCostKeys * 4,
                   hipMemcpyHostToDevice) != hipSuccess ||
-        hipMemcpy(S->e.order_ctl, zeros.data(), 2 * 4, hipMemcpyHostToDevice) != hipSuccess) {
+        hipMemcpy(S->e.order_ctl, zeros.data(), kOrderCtlWords * 4, hipMemcpyHostToDevice) !=
+            hipSuccess) {
         (void)hipHostFree(S->pinned);
         (void)hipFree(S->dev_base);
         return fail(LIK_EDEVICE, "stream or slot initialisation failed");
