@@ -139,10 +139,22 @@ struct GroupLaunch {
     unsigned max_items = 0;          // upper bound on the group's work items
 };
 
+// Streams beside an engine's own for the launches of an iteration's further
+// groups, and the events that fork and join them.
+struct SideStreams {
+    static constexpr int kN = 2;
+    hipStream_t st[kN] = {};
+    hipEvent_t fork = nullptr, join[kN] = {};
+    hipError_t create();
+    void destroy();
+};
+
 // One iteration: order the work, propagate every group, weigh/resample.
 // `timed`: bracket the launches with timing events while timing is enabled.
+// side: the groups' launches run beside each other, between the ordering and
+// the weighing (null, or while timing: one after the other on s).
 hipError_t engine_iteration(const EngineArgs &e, const GroupLaunch *groups, int n_groups,
-                            hipStream_t s, bool timed = true);
+                            hipStream_t s, bool timed = true, SideStreams *side = nullptr);
 
 // The specialised kernel if the variant and the amount of work call for it.
 // Returns false only when LIK_KERNEL_SPECIALIZED was asked for and failed.

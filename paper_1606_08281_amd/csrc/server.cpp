@@ -143,6 +143,7 @@ struct lik_server {
     int device = 0;
     bool persistent = false;  // persistent propagation kernels for small networks
     hipStream_t stream = nullptr;
+    SideStreams side;               // the groups of one iteration beside each other
     char *dev_base = nullptr;       // engine table + arena
     char *arena = nullptr;
     size_t arena_bytes = 0;
@@ -449,7 +450,7 @@ void worker_main(lik_server *S) {
         S->e.f_lo = 0;
         S->e.f_hi = (int32_t)S->slots.high_water();
         S->e.pool_chunks = chunks;  // groups of 64 particles of the slots still running
-        if (engine_iteration(S->e, launches, kMaxGroups, S->stream) != hipSuccess)
+        if (engine_iteration(S->e, launches, kMaxGroups, S->stream, true, &S->side) != hipSuccess)
             S->worker_error = "iteration launch failed";
         S->e.order_parity ^= 1;  // admissions add their estimates to the next iteration's sum
         S->n_iterations += 1;
@@ -564,12 +565,14 @@ int lik_server_create(const lik_server_opts *opts, lik_server_t *out) {
     std::vector<uint32_t> stopped(slots, kFlagStopped);
     // the ordering passes' counts start at zero (each iteration leaves them so)
     std::vector<uint32_t> zeros(kMaxGroups * kCostKeys, 0u);
-    if (hipStreamCreate(&S->stream) != hipSuccess ||
+    if (hipStreamCreate(&S->stream) != hipSuccess || S->side.create() != hipSuccess ||
         hipMemcpy(S->e.fflags, stopped.data(), slots * 4, hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(S->e.order_count, zeros.data(), kMaxGroups * kCostKeys * 4,
                   hipMemcpyHostToDevice) != hipSuccess ||
         hipMemcpy(S->e.order_ctl, zeros.data(), kOrderCtlWords * 4, hipMemcpyHostToDevice) !=
             hipSuccess) {
+        S->side.destroy();
+        if (S->stream) (void)hipStreamDestroy(S->stream);
         (void)hipHostFree(S->pinned);
         (void)hipFree(S->dev_base);
         return fail(LIK_EDEVICE, "stream or slot initialisation failed");
@@ -679,6 +682,7 @@ int lik_server_destroy(lik_server_t S) {
     }
     if (S->worker.joinable()) S->worker.join();
     (void)hipStreamSynchronize(S->stream);
+    S->side.destroy();
     (void)hipStreamDestroy(S->stream);
     (void)hipHostFree(S->pinned);
     (void)hipFree(S->dev_base);
