@@ -126,6 +126,8 @@ int lik_create_network(int32_t n_species, int32_t n_reactions, const int32_t *re
  * counts and its order are staged in 6 KiB of LDS).  Idle lanes take new
  * particles once refill_min of them are idle; a pool's particles are taken
  * heaviest first (by the total propensity of their starting counts).
+ * While the GPU has room, filters expected to need many events are cut finer
+ * than a group of 64, down to items of 4 particles (not under persistent).
  */
 typedef struct lik_tuning {
     int32_t pool_min;      /* >= 1 */
@@ -605,9 +607,10 @@ typedef struct lik_ode_data {
  * constant indices, cached on disk like the networks' kernels; LIK_EDEVICE if
  * that fails) or LIK_KERNEL_AUTO (specialised, else generic); every variant
  * gives identical results.  Each (theta, trajectory) pair is integrated by
- * one GPU lane; the lanes take pairs from a shared counter, the trajectories
- * with the most stops (observations plus input breakpoints) first, which
- * changes only the speed.  Synchronous; allocates its device memory.
+ * one GPU lane (up to 49,152 pairs, specialised: by a group of 16 or 32); the
+ * lanes take pairs from a shared counter, the trajectories with the most
+ * stops (observations plus input breakpoints) first, which changes only the
+ * speed.  Synchronous; allocates its device memory.
  */
 int lik_ode_eval(lik_ode_t model, int32_t n_theta, const double *theta,
                  const lik_ode_data *data, double rtol, double atol, int32_t max_steps,

@@ -602,11 +602,27 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
         __builtin_amdgcn_s_setprio(1);
     }
     // (an item of at most 32 particles goes to the drain at once)
+    // A network of more than kBranchMax reactions leaves two wavefronts on a
+    // SIMD, where the branches of ssa_event cost more than they skip: 512 rate
+    // vectors of the 20 x 40 network 846 -> 803 ms with event_masked.  Six
+    // wavefronts hide them (telegraph: 323 ms, 335 with event_masked; Lac-Gfp,
+    // 18 reactions, 570 and 574).
+    constexpr int kBranchMax = 24;
+    double lim = have ? t_end : -__builtin_inf();
     while (p1 - p0 > kPropBlock / 2) {
-        if (have)
-            ssa_event<NetT, UMAX, RMAX, W, PREC, Real>(
-                net, c, x, S, t_end, event_cap, clock, n, st, a0_end, have, nu_tab,
-                [&] { return event_draw_uniform<PREC>(n, (uint32_t)j, c2, c3, k0, k1); });
+        if constexpr (RMAX > kBranchMax) {
+            const EventDraw<PREC> dr = event_draw_uniform<PREC>(n, (uint32_t)j, c2, c3, k0, k1);
+            have = event_masked<NetT, UMAX, RMAX, W, PREC, Real>(
+                net, c, x, S, lim, event_cap, clock, n, st, a0_end, nu_tab, dr.nl, dr.u2);
+            if constexpr (PREC == LIK_FP32_MIXED)
+                have = event_masked<NetT, UMAX, RMAX, W, PREC, Real>(
+                    net, c, x, S, lim, event_cap, clock, n, st, a0_end, nu_tab, dr.nl1, dr.u21);
+        } else {
+            if (have)
+                ssa_event<NetT, UMAX, RMAX, W, PREC, Real>(
+                    net, c, x, S, t_end, event_cap, clock, n, st, a0_end, have, nu_tab,
+                    [&] { return event_draw_uniform<PREC>(n, (uint32_t)j, c2, c3, k0, k1); });
+        }
         // Once at least refill_min lanes are idle (or all are), the idle
         // lanes store what they hold and take the next particles of the
         // pool, in lane order.
@@ -625,6 +641,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
                         have = true;
                         pend = true;
                         load_lds(nj - p0);
+                        lim = t_end;
                     }
                 }
                 next += n_idle;
@@ -656,7 +673,7 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
                   "drain buffers fit the pool's LDS");
     __syncthreads();  // every read of the staged counts is done
     uint64_t busy = __builtin_amdgcn_ballot_w64(have);
-    double lim = have ? t_end : -__builtin_inf();
+    lim = have ? t_end : -__builtin_inf();
     while (busy != 0ull) {
         const int k = (int)__popcll(busy);  // <= 32
         const int D = kPropBlock / k;       // >= 2
