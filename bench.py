@@ -516,26 +516,20 @@ def main():
 
     evals = wl.n_theta * args.steps
     model_ope = ops_per_event(wl.net.R, wl.net.U, args.precision)
-    # measured lane-op issue time per event (the committed counter record of
-    # this kernel, configuration and sources), else the model count
-    ope, ope_basis = model_ope, "model count at measured instruction costs (no counter record " \
-                                "matches the current kernel sources)"
-    passes = None
+    # The roofline counts the events' own work.  The committed counter record
+    # of this kernel, configuration and sources is reported beside it: its
+    # passes hold the lanes that a branch-free event masks off (a third of them
+    # on Lac-Gfp), so a fraction of it would count idle lanes as work.
+    ope, ope_basis = model_ope, "model count at measured instruction costs"
+    passes, issue_time = None, None
     if args.kernel in (0, 2) and not args.tuning and not args.autotune:
         from paper_1606_08281_amd import profsum
-        rec_name = f"{kname}_valu_{wl_tag}_{fp}.txt"
-        rec = profsum.read_record(os.path.join(ROOT, "profiles", rec_name))
+        rec = profsum.read_record(os.path.join(ROOT, "profiles",
+                                               f"{kname}_valu_{wl_tag}_{fp}.txt"))
         if rec is not None:
             passes = float(rec["lane_slots_per_event"])
-        if rec is not None and "lane_time_slots_per_event" in rec:
-            ope = float(rec["lane_time_slots_per_event"])
-            ope_basis = ("measured: SQ_THREAD_CYCLES_VALU / SSA events of this kernel on these "
-                         "sources, issue passes priced at the issue time per pass of its "
-                         "instruction classes (profiles/" + rec_name + ")")
-        elif rec is not None:
-            ope = float(rec["lane_slots_per_event"])
-            ope_basis = ("measured: SQ_THREAD_CYCLES_VALU / SSA events of this kernel on these "
-                         "sources, issue passes (profiles/" + rec_name + ")")
+            if "lane_time_slots_per_event" in rec:
+                issue_time = float(rec["lane_time_slots_per_event"])
     prop_s = tm["propagate_ms"] / 1e3
     # A replayed graph records no per-kernel events: its roofline is taken
     # over the whole step instead (a lower bound for the kernel's).
@@ -584,6 +578,7 @@ def main():
             "ops_per_event": ope,
             "ops_per_event_basis": ope_basis,
             "issue_passes_per_event": passes,
+            "issue_time_slots_per_event": issue_time,
             "model_ops_per_event": model_ope,
             "model_frac": events * model_ope / prop_s / 1e12 / peak,
             "traffic_unit": "HBM bytes per launch (FETCH_SIZE + WRITE_SIZE, copy-calibrated)",

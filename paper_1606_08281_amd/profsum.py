@@ -349,7 +349,9 @@ def main():
         # the bench line's launches: events per launch at its average launch time
         ev_b = bench["events_per_step"] * bench["steps"] / max(rl["launches"], 1)
         rate = ev_b / (rl["avg_launch_ms"] / 1e3)
-        lines.append(f"- VALU fraction of the bench line's launches: {rate:.4g} events/s x "
+        lines.append("- issue slots of the bench line's launches, masked-off lanes included (above 1 "
+                     "where a class of fast instructions is priced too high; not a fraction of "
+                     f"useful work): {rate:.4g} events/s x "
                      f"{vw['lane_time_slots_per_event']:.2f} slots / {rl['peak']:.2f} T = "
                      f"{rate * vw['lane_time_slots_per_event'] / (rl['peak'] * 1e12):.3f} "
                      f"(issue passes alone: "
