@@ -268,15 +268,9 @@ lik_ode_t_::Spec ode_spec_kernel(lik_ode_t_ &md, std::string *err) {
     std::lock_guard<std::mutex> g(md.mu);
     auto it = md.spec.find(dev);
     if (it != md.spec.end()) return it->second;
-    std::vector<char> code;
-    if (!rtc_code(ode_spec_source(md.m), &code, err)) return {};
     lik_ode_t_::Spec s;
-    hipError_t e = hipModuleLoadData(&s.mod, code.data());
-    if (e != hipSuccess) {
-        *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e);
-        return {};
-    }
-    e = hipModuleGetFunction(&s.fn, s.mod, "lik_ode_spec");
+    if (!load_source(ode_spec_source(md.m), &s.mod, err)) return {};
+    hipError_t e = hipModuleGetFunction(&s.fn, s.mod, "lik_ode_spec");
     if (e == hipSuccess && ode_group_lanes(md.m))
         e = hipModuleGetFunction(&s.group, s.mod, "lik_ode_group");
     if (e != hipSuccess) {
@@ -522,9 +516,8 @@ int lik_ode_create(const lik_ode_model *model, lik_ode_t *out) {
 
 int lik_ode_precompile(lik_ode_t model) {
     if (!model) return fail(LIK_EINVAL, "model is NULL");
-    std::vector<char> code;
     std::string err;
-    if (!rtc_code(ode_spec_source(model->m), &code, &err)) return fail(LIK_EDEVICE, err);
+    if (!precompile_source(ode_spec_source(model->m), &err)) return fail(LIK_EDEVICE, err);
     return LIK_OK;
 }
 

@@ -246,18 +246,6 @@ std::string specialized_source(const lik_network &net, int precision) {
 
 namespace {
 
-// Code object of a generated source: from the disk cache or compiled now.
-bool code_for_source(const std::string &src, std::vector<char> *code, std::string *path_out,
-                     std::string *err);
-
-// Code object for (network, precision): from the disk cache or compiled now.
-bool specialized_code(const lik_network &net, int precision, std::vector<char> *code,
-                      std::string *src_out, std::string *path_out, std::string *err) {
-    const std::string src = specialized_source(net, precision);
-    *src_out = src;
-    return code_for_source(src, code, path_out, err);
-}
-
 // The disk cache's file for a generated source.
 std::string cache_path(const std::string &src) {
     // the key covers everything the code object depends on: the generated
@@ -276,10 +264,9 @@ std::string cache_path(const std::string &src) {
     return cache_dir() + "/prop_" + hex + ".co";
 }
 
-bool code_for_source(const std::string &src, std::vector<char> *code, std::string *path_out,
-                     std::string *err) {
+// Code object of a generated source: from the disk cache or compiled now.
+bool code_for_source(const std::string &src, std::vector<char> *code, std::string *err) {
     const std::string dir = cache_dir(), path = cache_path(src);
-    *path_out = path;
     if (read_file(path, code)) return true;
     if (!compile(src, code, err)) return false;
     write_file_atomic(dir, path, *code);
@@ -289,9 +276,7 @@ bool code_for_source(const std::string &src, std::vector<char> *code, std::strin
 }  // namespace
 
 bool precompile_specialized(const lik_network &net, int precision, std::string *err) {
-    std::vector<char> code;
-    std::string src, path;
-    return specialized_code(net, precision, &code, &src, &path, err);
+    return precompile_source(specialized_source(net, precision), err);
 }
 
 hipFunction_t specialized_kernel(lik_network &net, int precision, std::string *err,
@@ -308,26 +293,11 @@ hipFunction_t specialized_kernel(lik_network &net, int precision, std::string *e
     };
     if (it != net.spec.end()) return pick(it->second);
 
-    std::vector<char> code;
-    std::string src, path;
-    if (!specialized_code(net, precision, &code, &src, &path, err)) return nullptr;
-    const std::string dir = cache_dir();
     hipModule_t mod = nullptr;
-    hipError_t e = hipModuleLoadData(&mod, code.data());
-    if (e != hipSuccess) {
-        // a damaged cache entry: compile afresh once
-        code.clear();
-        if (!compile(src, &code, err)) return nullptr;
-        write_file_atomic(dir, path, code);
-        e = hipModuleLoadData(&mod, code.data());
-        if (e != hipSuccess) {
-            *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e);
-            return nullptr;
-        }
-    }
+    if (!load_source(specialized_source(net, precision), &mod, err)) return nullptr;
     lik_network::SpecKernels k;
     k.mod = mod;
-    e = hipModuleGetFunction(&k.item, mod, "lik_propagate_spec");
+    hipError_t e = hipModuleGetFunction(&k.item, mod, "lik_propagate_spec");
     if (e != hipSuccess) {
         *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e);
         (void)hipModuleUnload(mod);
@@ -382,15 +352,31 @@ bool specialized_multi_available(const std::vector<lik_network *> &nets, int pre
     return access(path.c_str(), R_OK) == 0;
 }
 
-bool rtc_code(const std::string &src, std::vector<char> *code, std::string *err) {
-    std::string path;
-    return code_for_source(src, code, &path, err);
+bool load_source(const std::string &src, hipModule_t *mod, std::string *err) {
+    std::vector<char> code;
+    if (!code_for_source(src, &code, err)) return false;
+    if (hipModuleLoadData(mod, code.data()) == hipSuccess) return true;
+    // a damaged cache entry: compile afresh once.  A failed load also leaves
+    // its error for the next launch check to find, which would fail a call that
+    // goes on without the kernel.
+    (void)hipGetLastError();
+    code.clear();
+    if (!compile(src, &code, err)) return false;
+    write_file_atomic(cache_dir(), cache_path(src), code);
+    const hipError_t e = hipModuleLoadData(mod, code.data());
+    if (e == hipSuccess) return true;
+    (void)hipGetLastError();
+    *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e);
+    return false;
+}
+
+bool precompile_source(const std::string &src, std::string *err) {
+    std::vector<char> code;
+    return code_for_source(src, &code, err);
 }
 
 bool precompile_multi(const std::vector<lik_network *> &nets, int precision, std::string *err) {
-    std::vector<char> code;
-    std::string path;
-    return code_for_source(specialized_multi_source(nets, precision), &code, &path, err);
+    return precompile_source(specialized_multi_source(nets, precision), err);
 }
 
 hipFunction_t specialized_multi_kernel(const std::vector<lik_network *> &nets, int precision,
@@ -404,17 +390,10 @@ hipFunction_t specialized_multi_kernel(const std::vector<lik_network *> &nets, i
     std::lock_guard<std::mutex> g(g_multi_mu);
     auto it = g_multi.find({dev, src});
     if (it != g_multi.end()) return it->second.second;
-    std::vector<char> code;
-    std::string path;
-    if (!code_for_source(src, &code, &path, err)) return nullptr;
     hipModule_t mod = nullptr;
-    hipError_t e = hipModuleLoadData(&mod, code.data());
-    if (e != hipSuccess) {
-        *err = std::string("hipModuleLoadData: ") + hipGetErrorString(e);
-        return nullptr;
-    }
+    if (!load_source(src, &mod, err)) return nullptr;
     hipFunction_t fn = nullptr;
-    e = hipModuleGetFunction(&fn, mod, "lik_flow_spec_multi");
+    const hipError_t e = hipModuleGetFunction(&fn, mod, "lik_flow_spec_multi");
     if (e != hipSuccess) {
         *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e);
         (void)hipModuleUnload(mod);
