@@ -400,7 +400,7 @@ size_t lik_workspace_size(lik_network_t net, int32_t n_theta, int32_t n_traj,
     b += align256(F * 4) * 4;                 // tcur, fstatus, fflags, cost
     b += align256(F);                         // pool
     b += align256(F * 8) * 2;                 // fll, fevents
-    b += align256(item_list_capacity(F * (Hp / 64)) * 4);  // items
+    b += align256(F * (Hp / 64) * 4);         // items
     b += align256(kMaxGroups * 4);            // item_count
     b += align256(kMaxGroups * 4);            // item_cursor
     b += 2 * align256(kMaxGroups * kCostKeys * 4) + align256(kOrderCtlWords * 4);  // ordering passes
@@ -637,8 +637,7 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
     // takes the per-interval schedule, with the same results
     const size_t items_max = (size_t)n_theta * (size_t)total * (size_t)nchunk;
     bool flow = net->tuning.schedule == 1 && items_max < ((size_t)1 << 26);
-    EngineLayout L = carve_engine(p, F, item_list_capacity(F * nchunk),
-                                  request_state_bytes((int64_t)F, net->U, Hp),
+    EngineLayout L = carve_engine(p, F, F * nchunk, request_state_bytes((int64_t)F, net->U, Hp),
                                   flow_ring_capacity(F, nchunk));
     L.e.f_lo = 0;
     L.e.f_hi = (int32_t)F;
@@ -685,7 +684,8 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
                             : specialized_kernel(*net, precision, &err, kSpecPersistent);
 
     if (!G.persistent) {  // the per-interval schedule's splitting
-        if (F * nchunk < kSplitChunks) {  // (the item list has room)
+        if (F * nchunk < kSplitChunks) {
+            L.e.items = reinterpret_cast<uint32_t *>(L.fa.ring);
             L.e.split_goal = split_goal(F);
             L.e.split_budget = (int32_t)split_waves();
             G.max_items += split_waves();

@@ -231,23 +231,25 @@ int flow_blocks_per_cu(int umax, int rmax, int precision);  // resident flow wav
 // The flow schedule hides each hand-off's latency behind other resident
 // wavefronts: below this many per CU it is slower than the per-interval one.
 constexpr int kFlowMinWavesPerCu = 16;
-// Ring capacity for F slots of nchunk groups of 64 particles.
+// Ring capacity for F slots of nchunk groups of 64 particles: one interval of
+// every filter, and the at most 4096 items (split_waves) that splitting may
+// add to it.
+constexpr uint32_t kFlowRingMin = 8192;
 inline uint32_t flow_ring_capacity(size_t F, int nchunk) {
     const size_t need = 2 * F * (size_t)nchunk;
-    // one interval of every filter, and the at most 4096 items (split_waves)
-    // that splitting may add to it
-    uint32_t c = 8192;
+    uint32_t c = kFlowRingMin;
     while ((size_t)c < need && c < (1u << 31)) c <<= 1;
     return c;
 }
 
-// Room in the per-interval schedule's item list for `chunks` groups of 64.  A
-// list below kSplitChunks groups may split them (kSplitWavesPerCu per CU more
-// items at most); larger ones fill the GPU without.
+// A per-interval iteration of fewer groups of 64 than this may split them;
+// larger ones fill the GPU without.  Its item list, with the at most 4096 items
+// that splitting adds, takes the place of the rings, which that schedule does
+// not use: a workspace then never needs more bytes for a smaller batch.
 constexpr size_t kSplitChunks = 2048;
-inline size_t item_list_capacity(size_t chunks) {
-    return chunks < kSplitChunks ? kSplitChunks + 4096 : chunks;
-}
+static_assert((kSplitChunks + 4096) * sizeof(uint32_t) <=
+                  (size_t)kFlowRingMin * sizeof(uint64_t) * kFlowRings,
+              "the split items fit the rings");
 
 // Per-request setup / results.  A request is n_theta rate vectors against M
 // trajectories, occupying slots base .. base + n_theta*M - 1.
