@@ -64,8 +64,14 @@ int32_t lik::split_goal(size_t slots) {
 int32_t lik::flow_spare(int64_t intervals, int h_max, int64_t items_max) {
     const int64_t least = kPropBlock >> kSplitMax;  // particles of the smallest item
     const int64_t most = intervals * ((h_max + least - 1) / least);
-    // an empty wavefront costs its dispatch, 0.25 ns: bounded
-    return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, 1 << 20));
+    // an empty wavefront costs its dispatch, 0.25 ns: bounded, and by what one
+    // launch takes (with none to spare, settle_spare splits no interval)
+    const int64_t room = std::min<int64_t>(1 << 20, kMaxLaunchWaves - items_max);
+    return (int32_t)std::max<int64_t>(0, std::min<int64_t>(most - items_max, room));
+}
+
+int32_t lik::split_budget(int64_t chunks) {
+    return chunks + split_waves() <= kMaxLaunchWaves ? (int32_t)split_waves() : 0;
 }
 
 namespace {
@@ -636,7 +642,7 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
     // interval of every filter in groups of 64); beyond 2^26 of them the batch
     // takes the per-interval schedule, with the same results
     const size_t items_max = (size_t)n_theta * (size_t)total * (size_t)nchunk;
-    bool flow = net->tuning.schedule == 1 && items_max < ((size_t)1 << 26);
+    bool flow = net->tuning.schedule == 1 && items_max <= (size_t)kMaxLaunchWaves;
     EngineLayout L = carve_engine(p, F, F * nchunk, request_state_bytes((int64_t)F, net->U, Hp),
                                   flow_ring_capacity(F, nchunk));
     L.e.f_lo = 0;

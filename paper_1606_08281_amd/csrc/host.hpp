@@ -114,9 +114,14 @@ uint32_t compute_units();  // of the current device
 uint32_t split_waves();
 // An even share of those items per slot for the per-interval schedule (0: none).
 int32_t split_goal(size_t slots);
+// Wavefronts of one launch: it takes fewer than 2^32 lanes.
+constexpr int64_t kMaxLaunchWaves = ((int64_t)1 << 26) - 1;
+// Items that splitting may add to a per-interval iteration of at most `chunks`
+// groups of 64 particles.
+int32_t split_budget(int64_t chunks);
 // Wavefronts a flow launch takes beyond one per group of 64 particles, so that
 // every interval can be split: `intervals` filter-intervals of at most h_max
-// particles with items_max groups in all.
+// particles with items_max (<= kMaxLaunchWaves) groups in all.
 int32_t flow_spare(int64_t intervals, int h_max, int64_t items_max);
 unsigned persistent_waves();  // grid of the persistent propagation kernels
 bool tuning_valid(const lik_tuning &t);

@@ -255,7 +255,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
 
     // schedule and kernels
     std::string msg;
-    bool flow = tu.schedule == 1 && items_max < ((int64_t)1 << 26);
+    bool flow = tu.schedule == 1 && items_max <= kMaxLaunchWaves;
     hipFunction_t spec_multi = nullptr;
     if (flow) {
         int per_cu = 0;
@@ -305,7 +305,7 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
             need[(size_t)plan[(size_t)k].group] += plan[(size_t)k].F * (plan[(size_t)k].Hp / 64);
         if (!tu.persistent) {
             e.split_goal = split_goal((size_t)F);
-            e.split_budget = (int32_t)split_waves();
+            e.split_budget = split_budget(chunks);
         }
         uint32_t off = 0;
         for (size_t g = 0; g < nets.size(); ++g) {

@@ -439,6 +439,7 @@ void worker_main(lik_server *S) {
             }
         S->e.h_max = h_max;
         S->e.split_goal = S->persistent ? 0 : split_goal(running);
+        S->e.split_budget = S->persistent ? 0 : split_budget(chunks);
         unsigned off = 0;
         for (int g = 0; g < kMaxGroups; ++g) {
             if (need[g]) need[g] += (unsigned)S->e.split_budget;  // room for split items

@@ -1,0 +1,120 @@
+// Runs entry points of liblik without a GPU: the HIP calls they make are
+// answered here (this program's definitions come before the runtime's), device
+// memory is host memory that no kernel touches, and every kernel launch is
+// printed as "name blocks threads stream".
+//   batch n_theta n_obs n_particles schedule
+//   requests n_theta n_obs n_particles schedule
+#define __HIP_PLATFORM_AMD__ 1
+#include <cxxabi.h>
+#include <dlfcn.h>
+#include <hip/hip_runtime.h>
+#include <stdio.h>
+#include <stdlib.h>
+#include <string.h>
+
+#include <string>
+#include <vector>
+
+#include "../../include/lik.h"
+
+namespace {
+dim3 g_grid, g_block;
+hipStream_t g_stream;
+
+std::string kernel_name(const void *fn) {
+    Dl_info info;
+    if (!dladdr(fn, &info) || !info.dli_sname) return "?";
+    int st = 0;
+    char *d = abi::__cxa_demangle(info.dli_sname, nullptr, nullptr, &st);
+    std::string s = st == 0 ? d : info.dli_sname;
+    free(d);
+    const size_t at = s.find("k_");
+    size_t end = at;
+    while (end < s.size() && (isalnum((unsigned char)s[end]) || s[end] == '_')) ++end;
+    return at == std::string::npos ? s : s.substr(at, end - at);
+}
+}  // namespace
+
+extern "C" {
+hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
+hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int *v, hipDeviceAttribute_t a, int) {
+    *v = a == hipDeviceAttributeMultiprocessorCount ? 256 : 100000;
+    return hipSuccess;
+}
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) {
+    *s = hipStreamCaptureStatusNone;
+    return hipSuccess;
+}
+hipError_t hipMalloc(void **p, size_t n) { *p = malloc(n); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipFree(void *p) { free(p); return hipSuccess; }
+hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
+hipError_t hipStreamCreate(hipStream_t *s) { *s = (hipStream_t)0x10; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {
+    *n = 24;
+    return hipSuccess;
+}
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t, hipStream_t s) {
+    g_grid = g;
+    g_block = b;
+    g_stream = s;
+    return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3 *g, dim3 *b, size_t *n, hipStream_t *s) {
+    *g = g_grid;
+    *b = g_block;
+    *n = 0;
+    *s = g_stream;
+    return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipStream_t s) {
+    printf("%s %u %u %p\n", kernel_name(fn).c_str(), g.x, b.x, (void *)s);
+    return hipSuccess;
+}
+}
+
+int main(int argc, char **argv) {
+    if (argc != 6) return 2;
+    const std::string what = argv[1];
+    const int n = atoi(argv[2]), T = atoi(argv[3]), H = atoi(argv[4]), schedule = atoi(argv[5]);
+    const int32_t orders[2] = {0, 1}, stoich[2] = {1, -1};  // immigration and death
+    lik_network_t net = nullptr;
+    if (lik_create_network(1, 2, orders, stoich, &net) != LIK_OK) return 3;
+    lik_tuning tu;
+    lik_network_get_tuning(net, &tu);
+    tu.schedule = schedule;
+    lik_network_set_tuning(net, &tu);
+    std::vector<double> theta((size_t)n * 2, 0.0), t(T), y(T, 1.0), ll(n);
+    std::vector<int32_t> st(n);
+    for (int k = 0; k < T; ++k) t[k] = k + 1.0;
+    const int32_t offs[2] = {0, T}, x0[1] = {1};
+    const double t0[1] = {0.0};
+    const lik_data data = {1, offs, t.data(), y.data(), t0, x0, nullptr};
+    lik_obs_model obs;
+    memset(&obs, 0, sizeof(obs));
+    obs.kind = LIK_OBS_GAUSSIAN;
+    obs.n_observed = 1;
+    obs.sigma = 1.0;
+    int rc = LIK_OK;
+    if (what == "batch") {
+        const lik_eval_opts o = {LIK_FP64, LIK_KERNEL_GENERIC, 0, nullptr, 0, 0};
+        const size_t bytes = lik_workspace_size(net, n, 1, H);
+        void *ws = malloc(bytes);
+        rc = lik_eval_batch_device(net, &obs, &o, n, theta.data(), &data, offs, H, 1, ll.data(),
+                                   st.data(), nullptr, ws, bytes, nullptr);
+    } else {
+        lik_request r;
+        memset(&r, 0, sizeof(r));
+        r.net = net;
+        r.obs = obs;
+        r.n_theta = n;
+        r.theta = theta.data();
+        r.data = data;
+        r.n_particles = H;
+        rc = lik_eval_requests(&r, 1, &tu, LIK_KERNEL_GENERIC, ll.data(), st.data(), nullptr);
+    }
+    if (rc != LIK_OK) printf("error %d %s\n", rc, lik_last_error());
+    return rc == LIK_OK ? 0 : 1;
+}

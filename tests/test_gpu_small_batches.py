@@ -103,3 +103,22 @@ def test_automatic_kernel_choice_under_capture():
         eager, _ = db.run(theta, wl.seed)
         torch.cuda.synchronize()
         assert torch.equal(replayed, eager)
+
+
+def test_flow_launch_near_2_to_32_lanes():
+    """A batch whose wavefronts, with any spare one beyond 2^26 - 1, would not
+    fit one launch: the same results as few of its filters in the per-interval
+    schedule."""
+    T = 65535
+    rng = np.random.default_rng(3)
+    wl = W.immigration_death_workload(1)
+    tr = dict(t_obs=np.arange(1, T + 1) * 1.0, y=rng.normal(5.0, 2.0, (T, 1)), t0=0.0,
+              x0=np.array([5], np.int32))
+    theta = np.exp(rng.normal([-9.0, -9.0], 0.5, (1024, 2)))
+    kw = dict(trajectories=[tr], H=5, kernel=1)
+    _say("flow launch of 1024 x 65535 items")
+    got = _gpu(wl, theta=theta, tuning={"schedule": 1}, **kw)
+    some = [0, 511, 1023]
+    want = _gpu(wl, theta=theta[some], theta_ids=some, tuning={"schedule": 0}, **kw)
+    assert np.array_equal(got["loglik"][some], want["loglik"])
+    assert np.all(got["status"] == 0)

@@ -1,5 +1,9 @@
 """What the host side plans before it launches, without a GPU: workspace
-sizes."""
+sizes, and the kernel launches of a call, recorded by a program that answers
+the HIP runtime's calls itself (helpers/launch_probe.cpp)."""
+import os
+import subprocess
+
 import numpy as np
 import pytest
 
@@ -27,3 +31,49 @@ def test_workspace_size_never_shrinks_with_the_batch(shape):
     shrinks = [n for n in range(1, 9000) if need[n] < need[n - 1]]
     assert not shrinks
     assert sum(b <= 64 << 20 for b in need) - 1 == SCRATCH_FITS[shape]
+
+
+HERE = os.path.dirname(os.path.abspath(__file__))
+
+
+@pytest.fixture(scope="module")
+def launches(tmp_path_factory):
+    """launches(*args): the calls' kernel launches, [(name, blocks, threads, stream)]."""
+    from paper_1606_08281_amd import build
+    exe = str(tmp_path_factory.mktemp("probe") / "launch_probe")
+    folder = os.path.dirname(os.path.abspath(lik.LIB_PATH))
+    subprocess.run(["g++", "-O1", "-std=c++17", "-rdynamic", "-I/opt/rocm/include", "-o", exe,
+                    os.path.join(HERE, "helpers", "launch_probe.cpp"), f"-L{folder}",
+                    "-l:liblik.so", f"-Wl,-rpath,{folder}:{build.hip_runtime_dir()}",
+                    "-Wl,--allow-shlib-undefined", "-ldl"], check=True)
+
+    def run(*args):
+        out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True)
+        rows = [line.split() for line in out.stdout.splitlines()]
+        return [(r[0], int(r[1]), int(r[2]), r[3]) for r in rows]
+    return run
+
+
+@pytest.mark.parametrize("entry", ["batch", "requests"])
+@pytest.mark.parametrize("filters,intervals", [(1, 20), (1024, 64511), (1024, 64512),
+                                               (1024, 65535), (4095, 16388)])
+def test_flow_launch_stays_below_2_to_32_lanes(launches, entry, filters, intervals):
+    """One wavefront per group of 64 particles of every interval, and spare
+    ones as far as a launch takes them (fewer than 2^32 lanes): up to, at and
+    beyond 2^26 - 2^20 groups."""
+    items = filters * intervals
+    assert items < 1 << 26
+    flow = [r for r in launches(entry, filters, intervals, 64, 1)
+            if r[0] in ("k_flow", "k_flow_multi")]
+    assert len(flow) == 1
+    _, blocks, threads, _ = flow[0]
+    assert threads == 64 and items <= blocks and blocks * threads < 1 << 32
+    # spare wavefronts: for every interval in items of 4 particles, at most 2^20
+    assert blocks == items + min(15 * items, 1 << 20, (1 << 26) - 1 - items)
+
+
+@pytest.mark.parametrize("entry", ["batch", "requests"])
+def test_more_groups_take_the_per_interval_schedule(launches, entry):
+    names = [r[0] for r in launches(entry, 8192, 1024, 512, 1)]   # 2^26 groups
+    assert "k_flow" not in names and "k_flow_multi" not in names
+    assert names.count("k_propagate") == 1024
