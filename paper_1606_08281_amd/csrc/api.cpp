@@ -510,7 +510,7 @@ hipError_t lik::engine_iteration(const EngineArgs &e, const GroupLaunch *groups,
     for (int g = 0; g < n_groups; ++g) active += groups[g].max_items > 0 ? 1 : 0;
     const bool beside = side && !timed && active > 1;
     if (beside && (err = hipEventRecord(side->fork, s)) != hipSuccess) return err;
-    for (int g = 0; g < n_groups; ++g) {
+    for (int g = 0; g < n_groups && err == hipSuccess; ++g) {
         const GroupLaunch &G = groups[g];
         if (G.max_items == 0) continue;
         hipStream_t gs = s;
@@ -518,7 +518,7 @@ hipError_t lik::engine_iteration(const EngineArgs &e, const GroupLaunch *groups,
             const int q = (k - 1) % SideStreams::kN;
             gs = side->st[q];
             if (q == used) {
-                if ((err = hipStreamWaitEvent(gs, side->fork, 0)) != hipSuccess) return err;
+                if ((err = hipStreamWaitEvent(gs, side->fork, 0)) != hipSuccess) break;
                 ++used;
             }
         }
@@ -534,13 +534,19 @@ hipError_t lik::engine_iteration(const EngineArgs &e, const GroupLaunch *groups,
         } else {
             err = launch_propagate(e, g, grid, G.netargs, G.umax, G.rmax, G.precision, pers, gs);
         }
-        if (err != hipSuccess) return err;
-        if (timed) g_timing.prop.push_back({e0, timing_mark(s)});
+        if (err == hipSuccess && timed) g_timing.prop.push_back({e0, timing_mark(s)});
     }
-    for (int q = 0; q < used; ++q)
-        if ((err = hipEventRecord(side->join[q], side->st[q])) != hipSuccess ||
-            (err = hipStreamWaitEvent(s, side->join[q], 0)) != hipSuccess)
-            return err;
+    // s waits for the groups launched beside it, also after a launch that
+    // failed: what the caller enqueues on s next may free or reuse their slots
+    for (int q = 0; q < used; ++q) {
+        hipError_t ej = hipEventRecord(side->join[q], side->st[q]);
+        if (ej == hipSuccess) ej = hipStreamWaitEvent(s, side->join[q], 0);
+        if (ej != hipSuccess) {
+            (void)hipStreamSynchronize(side->st[q]);
+            if (err == hipSuccess) err = ej;
+        }
+    }
+    if (err != hipSuccess) return err;
     hipEvent_t w0 = timed ? timing_mark(s) : nullptr;
     err = launch_weigh(e, s);
     if (err == hipSuccess && timed) g_timing.weigh.push_back({w0, timing_mark(s)});

@@ -4,6 +4,10 @@
 // printed as "name blocks threads stream".
 //   batch n_theta n_obs n_particles schedule
 //   requests n_theta n_obs n_particles schedule
+//   groups n_groups failing: one engine iteration of n_groups groups beside
+//     each other, the launch of group `failing` (-1: none) refused; stream
+//     records and waits are printed as "record stream" and "wait stream stream"
+//     (an event is named by the stream that recorded it last)
 #define __HIP_PLATFORM_AMD__ 1
 #include <cxxabi.h>
 #include <dlfcn.h>
@@ -12,14 +16,17 @@
 #include <stdlib.h>
 #include <string.h>
 
+#include <map>
 #include <string>
 #include <vector>
 
 #include "../../include/lik.h"
+#include "../../paper_1606_08281_amd/csrc/host.hpp"
 
 namespace {
 dim3 g_grid, g_block;
 hipStream_t g_stream;
+std::map<hipEvent_t, hipStream_t> g_recorded;
 
 std::string kernel_name(const void *fn) {
     Dl_info info;
@@ -51,6 +58,15 @@ hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 hipError_t hipStreamCreate(hipStream_t *s) { *s = (hipStream_t)0x10; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
+    g_recorded[e] = s;
+    printf("record %p\n", (void *)s);
+    return hipSuccess;
+}
+hipError_t hipStreamWaitEvent(hipStream_t s, hipEvent_t e, unsigned) {
+    printf("wait %p %p\n", (void *)s, (void *)g_recorded[e]);
+    return hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
 hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int *n, const void *, int, size_t) {
     *n = 24;
@@ -75,9 +91,33 @@ hipError_t hipLaunchKernel(const void *fn, dim3 g, dim3 b, void **, size_t, hipS
 }
 }
 
+static int iteration(int n, int failing) {
+    lik::EngineArgs e;
+    memset(&e, 0, sizeof(e));
+    e.f_hi = e.h_max = 1;
+    const lik::Net4x8 net{};
+    std::vector<lik::GroupLaunch> groups(n);
+    for (int g = 0; g < n; ++g) {
+        groups[g].umax = g == failing ? 5 : 4;  // no generic kernel has 5 species
+        groups[g].rmax = 8;
+        groups[g].netargs = &net;
+        groups[g].max_items = 1;
+    }
+    lik::SideStreams side;
+    side.fork = (hipEvent_t)0xf0;
+    for (int k = 0; k < lik::SideStreams::kN; ++k) {
+        side.st[k] = (hipStream_t)(size_t)(0x100 * (k + 1));
+        side.join[k] = (hipEvent_t)(size_t)(0xf1 + k);
+    }
+    const hipError_t err = lik::engine_iteration(e, groups.data(), n, (hipStream_t)0x10, false, &side);
+    printf("returned %d\n", (int)err);
+    return 0;
+}
+
 int main(int argc, char **argv) {
+    const std::string what = argc > 1 ? argv[1] : "";
+    if (what == "groups" && argc == 4) return iteration(atoi(argv[2]), atoi(argv[3]));
     if (argc != 6) return 2;
-    const std::string what = argv[1];
     const int n = atoi(argv[2]), T = atoi(argv[3]), H = atoi(argv[4]), schedule = atoi(argv[5]);
     const int32_t orders[2] = {0, 1}, stoich[2] = {1, -1};  // immigration and death
     lik_network_t net = nullptr;

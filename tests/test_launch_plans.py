@@ -47,10 +47,10 @@ def launches(tmp_path_factory):
                     "-l:liblik.so", f"-Wl,-rpath,{folder}:{build.hip_runtime_dir()}",
                     "-Wl,--allow-shlib-undefined", "-ldl"], check=True)
 
-    def run(*args):
+    def run(*args, raw=False):
         out = subprocess.run([exe, *map(str, args)], check=True, capture_output=True, text=True)
         rows = [line.split() for line in out.stdout.splitlines()]
-        return [(r[0], int(r[1]), int(r[2]), r[3]) for r in rows]
+        return rows if raw else [(r[0], int(r[1]), int(r[2]), r[3]) for r in rows]
     return run
 
 
@@ -77,3 +77,18 @@ def test_more_groups_take_the_per_interval_schedule(launches, entry):
     names = [r[0] for r in launches(entry, 8192, 1024, 512, 1)]   # 2^26 groups
     assert "k_flow" not in names and "k_flow_multi" not in names
     assert names.count("k_propagate") == 1024
+
+
+@pytest.mark.parametrize("failing", [-1, 0, 1, 2, 3])
+def test_groups_beside_each_other_are_always_waited_for(launches, failing):
+    """The server's iteration over four groups: its stream waits for every
+    stream that ran one, also when a group's launch fails; the next admission on
+    it may reuse the slots and memory of a finished request."""
+    rows = launches("groups", 4, failing, raw=True)
+    used = {r[3] for r in rows if r[0] == "k_propagate"} - {"0x10"}
+    waited = {r[2] for r in rows if r[0] == "wait" and r[1] == "0x10"}
+    assert used <= waited
+    assert (rows[-1] == ["returned", "0"]) == (failing < 0)
+    assert any(r[0] == "k_weigh" for r in rows) == (failing < 0)
+    if failing < 0:
+        assert used == {"0x100", "0x200"}
