@@ -776,7 +776,11 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
 
     hipStream_t s = (hipStream_t)stream;
     auto enqueue = [&](hipStream_t st) -> int {
-        hipError_t e = launch_admit(L.desc, L.e, r, st);
+        hipError_t e = hipSuccess;
+        // before the admission, which adds its estimates to the first iteration's sum
+        if (!flow && (e = launch_order_reset(L.e, st)) != hipSuccess)
+            return hip_fail(e, "order reset launch");
+        e = launch_admit(L.desc, L.e, r, st);
         if (e != hipSuccess) return hip_fail(e, "admit launch");
         if (r.x0_hi && (e = launch_init_start(L.desc, 0, (int32_t)F, st)) != hipSuccess)
             return hip_fail(e, "initial-count launch");
@@ -798,8 +802,6 @@ int eval_device(lik_network_t net, const lik_obs_model *obs, const lik_eval_opts
             e = launch_flow_check(L.e, L.fa, st);
             if (e != hipSuccess) return hip_fail(e, "flow check launch");
         } else {
-            e = launch_order_reset(L.e, st);
-            if (e != hipSuccess) return hip_fail(e, "order reset launch");
             for (int t = 0; t < t_max; ++t) {
                 EngineArgs it = L.e;
                 it.order_parity = t & 1;

@@ -215,7 +215,7 @@ __host__ __device__ inline const FlowArgs *flow_args_copy(uint32_t *ctl) {
 #ifndef __HIPCC_RTC__
 // Host-side launchers (kernels.hip).
 hipError_t launch_order(const EngineArgs &e, hipStream_t s);
-hipError_t launch_order_reset(const EngineArgs &e, hipStream_t s);  // before a batch's first
+hipError_t launch_order_reset(const EngineArgs &e, hipStream_t s);  // before a batch's admission
 constexpr int kOrderBlock = 256;  // slots per block of the ordering passes
 hipError_t launch_propagate(const EngineArgs &e, int group, unsigned n_items, const void *net,
                             int umax, int rmax, int precision, bool persistent, hipStream_t s);

@@ -340,6 +340,11 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
             rc = hip_fail(err, "copy to device");
             break;
         }
+        // before the admission, which adds its estimates to the first iteration's sum
+        if (!flow && (err = launch_order_reset(e, s)) != hipSuccess) {
+            rc = hip_fail(err, "order reset");
+            break;
+        }
         err = launch_admit_requests(desc, e, (const RequestArgs *)(dev + o_reqs),
                                     (const int32_t *)(dev + o_fstart), n_req, (int32_t)F,
                                     (uint64_t *)(dev + o_start), s);
@@ -365,7 +370,6 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
             timing_end_propagate(t0, s);
             if ((err = launch_flow_check(e, fa, s)) != hipSuccess) { rc = hip_fail(err, "flow check"); break; }
         } else {
-            if ((err = launch_order_reset(e, s)) != hipSuccess) { rc = hip_fail(err, "order reset"); break; }
             for (int t = 0; t < t_max && err == hipSuccess; ++t) {
                 e.order_parity = t & 1;
                 err = engine_iteration(e, groups, (int)nets.size(), s);

@@ -92,3 +92,14 @@ def test_groups_beside_each_other_are_always_waited_for(launches, failing):
     assert any(r[0] == "k_weigh" for r in rows) == (failing < 0)
     if failing < 0:
         assert used == {"0x100", "0x200"}
+
+
+@pytest.mark.parametrize("entry,admit", [("batch", "k_admit"), ("requests", "k_admit_requests")])
+def test_ordering_sums_are_cleared_before_the_admission(launches, entry, admit):
+    """The admission adds its estimates to the first interval's sum of expected
+    events; clearing the sums after it would throw them away (and leave it
+    adding to memory that nothing has set)."""
+    names = [r[0] for r in launches(entry, 4, 3, 64, 0)]
+    assert names.count("k_order_reset") == 1
+    assert names.index("k_order_reset") < names.index(admit) < names.index("k_order_count")
+    assert "k_order_reset" not in [r[0] for r in launches(entry, 4, 3, 64, 1)]
