@@ -60,9 +60,10 @@ extern "C" {
 #define LIK_STATUS_BAD_THETA 3      /* a rate was negative, infinite or NaN, or (with
                                        LIK_FP32_MIXED) beyond the binary32 range */
 #define LIK_STATUS_SCHEDULER 4      /* the flow schedule saw no work item finish for a
-                                       minute and gave up (an internal fault; the limit,
-                                       in microseconds, can be lowered through the
-                                       environment variable LIK_FLOW_STALL_US for tests) */
+                                       minute and gave up, within two (an internal fault;
+                                       the limit, in microseconds, can be lowered through
+                                       the environment variable LIK_FLOW_STALL_US for
+                                       tests) */
 #define LIK_STATUS_CANCELLED 5      /* server: the request was cancelled (lik_server_cancel) */
 #define LIK_STATUS_TIMED_OUT 6      /* server: the request's own time limit passed first */
 #define LIK_STATUS_STEP_LIMIT 7     /* deterministic model: the solver's step limit was reached */

@@ -62,26 +62,52 @@ __device__ __forceinline__ uint32_t ctl_load(const FlowArgs &fa, int w) {
     return __hip_atomic_load(&fa.ctl[w], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Progress of the launch: intervals finished (in items) and items claimed (a
-// wavefront that finishes its item leaves, and the next one claims).
+// Progress of the launch that a waiting wavefront polls: items of finished
+// intervals and items claimed (a wavefront that finishes its item leaves, and
+// the next one claims).
 __device__ __forceinline__ uint32_t flow_progress(const FlowArgs &fa) {
     return ctl_load(fa, kCtlProgress) + ctl_load(fa, kCtlHead + 64 * kRingItems);
 }
 
-// Gives up (sets the abort word, which every waiting wavefront then sees)
-// once there has been no progress for stall_ticks.  `seen` and `since` carry
-// the wait's last progress count and its time.
-__device__ __forceinline__ bool flow_stalled(const FlowArgs &fa, uint32_t &seen,
-                                             uint64_t &since) {
+// What a wait has seen of the progress, and when.
+struct StallWatch {
+    uint32_t seen = 0;
+    uint64_t since = 0;
+    bool counted = false;  // `left` was taken at `since`
+    uint64_t left = 0;     // items not finished, over every filter's interval
+};
+
+__device__ __forceinline__ void watch_start(const FlowArgs &fa, StallWatch &w) {
+    w.since = wall_clock64();
+    w.seen = flow_progress(fa);
+}
+
+// Gives up (sets the abort word, which every waiting wavefront then sees) once
+// no item has finished for stall_ticks.  Where every wavefront left already
+// holds its item, no claim shows that items of a long interval finish one after
+// another: after stall_ticks without polled progress the filters' items left
+// are counted, and only a second count, stall_ticks later, with the same result
+// ends the flow (so it comes between one and two limits after the last item).
+__device__ __forceinline__ bool flow_stalled(const FlowArgs &fa, StallWatch &w) {
     if (ctl_load(fa, kCtlAbort) != 0u) return true;
     const uint32_t prog = flow_progress(fa);
     const uint64_t now = wall_clock64();
-    if (prog != seen) {
-        seen = prog;
-        since = now;
-    } else if (now - since > fa.stall_ticks) {
-        __hip_atomic_store(&fa.ctl[kCtlAbort], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return true;
+    if (prog != w.seen) {
+        w.seen = prog;
+        w.since = now;
+        w.counted = false;
+    } else if (now - w.since > fa.stall_ticks) {
+        uint64_t left = 0;
+#pragma unroll 4
+        for (int f = 0; f < fa.n_slots; ++f)
+            left += __hip_atomic_load(&fa.remaining[f], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        if (w.counted && left == w.left) {
+            __hip_atomic_store(&fa.ctl[kCtlAbort], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return true;
+        }
+        w.left = left;
+        w.counted = true;
+        w.since = now;
     }
     return false;
 }
@@ -95,8 +121,7 @@ __device__ __forceinline__ uint64_t *ring_slot(const FlowArgs &fa, int r, uint32
 // every filter is done.
 __device__ __forceinline__ bool ring_wait(const FlowArgs &fa, int r, uint32_t pos, uint32_t want,
                                           uint64_t *entry, bool until_done) {
-    uint64_t since = 0;
-    uint32_t seen = 0;
+    StallWatch watch;
     for (bool first = true;; first = false) {
         const uint64_t v =
             __hip_atomic_load(ring_slot(fa, r, pos), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -104,12 +129,9 @@ __device__ __forceinline__ bool ring_wait(const FlowArgs &fa, int r, uint32_t po
             *entry = v;
             return true;
         }
-        if (first) {
-            since = wall_clock64();
-            seen = flow_progress(fa);
-        }
+        if (first) watch_start(fa, watch);
         if (until_done && (int)ctl_load(fa, kCtlFinished) >= fa.n_slots) return false;
-        if (flow_stalled(fa, seen, since)) return false;
+        if (flow_stalled(fa, watch)) return false;
         __builtin_amdgcn_s_sleep(8);
     }
 }
@@ -285,8 +307,7 @@ __device__ __forceinline__ void flow_unpark_some(const EngineArgs &e, const Flow
 // one far from its turn sleeps longer and reads one of them.
 __device__ __forceinline__ int item_wait(const FlowArgs &fa, uint32_t pos, uint64_t *entry) {
     constexpr uint32_t kFar = 256;  // positions beyond the last item written
-    uint64_t since = 0;
-    uint32_t seen = 0;
+    StallWatch watch;
     bool far = false;
     for (uint32_t n = 0;; ++n) {
         const uint64_t v = __hip_atomic_load(ring_slot(fa, kRingItems, pos), __ATOMIC_RELAXED,
@@ -295,10 +316,7 @@ __device__ __forceinline__ int item_wait(const FlowArgs &fa, uint32_t pos, uint6
             *entry = v;
             return 1;
         }
-        if (n == 0) {
-            since = wall_clock64();
-            seen = flow_progress(fa);
-        }
+        if (n == 0) watch_start(fa, watch);
         if ((n & 7u) == 0u || far) {
             if ((int)ctl_load(fa, kCtlFinished) >= fa.n_slots) return 0;
         }
@@ -307,7 +325,7 @@ __device__ __forceinline__ int item_wait(const FlowArgs &fa, uint32_t pos, uint6
             if (tail == pos && (int32_t)(ctl_load(fa, kCtlTail + 64 * kRingParked) -
                                          ctl_load(fa, kCtlHead + 64 * kRingParked)) > 0)
                 return 2;
-            if (flow_stalled(fa, seen, since)) return 0;
+            if (flow_stalled(fa, watch)) return 0;
             far = (int32_t)(pos - tail) > (int32_t)kFar;
         }
         if (far)

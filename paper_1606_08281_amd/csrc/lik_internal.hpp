@@ -170,7 +170,7 @@ enum : int {
     kCtlHead = 0,         // + 64 r: next position of ring r a wavefront claims
     kCtlTail = 32,        // + 64 r: next position of ring r an entry is written to
     kCtlFinished = 128,   // slots that need no further interval
-    kCtlAbort = 160,      // nonzero: a wavefront saw no progress for stall_ticks
+    kCtlAbort = 160,      // nonzero: a wavefront saw no item finish for stall_ticks
     kCtlProgress = 192,   // work items of finished intervals
     kCtlSeedItems = 224,  // items of the first interval placed in the item ring
     kCtlSpare = 240,      // wavefronts of the launch no item needs so far (signed)
@@ -200,8 +200,9 @@ struct FlowArgs {
                              // over (0: no splitting)
     int32_t spare;           // wavefronts launched beyond one per group of 64 particles
     uint32_t pad;
-    uint64_t stall_ticks;  // wall-clock ticks without a finished item before a
-                           // waiting wavefront gives up (a scheduler fault)
+    uint64_t stall_ticks;  // wall-clock ticks without a finished item after which a
+                           // waiting wavefront gives up (a scheduler fault), within
+                           // twice as many
 };
 static_assert(sizeof(FlowArgs) <= 4 * (kCtlWords - kCtlArgs), "FlowArgs copy fits");
 // The flow kernel reads its FlowArgs from the copy in device memory: its

@@ -122,3 +122,28 @@ def test_flow_launch_near_2_to_32_lanes():
     want = _gpu(wl, theta=theta[some], theta_ids=some, tuning={"schedule": 0}, **kw)
     assert np.array_equal(got["loglik"][some], want["loglik"])
     assert np.all(got["status"] == 0)
+
+
+def test_long_interval_is_no_stall(monkeypatch):
+    """One filter whose interval lasts about twice the flow schedule's limit,
+    while its items (of 4 particles, started at different counts) finish one
+    after another and every wavefront of the launch is resident: not given up."""
+    import time
+    orders, stoich = np.array([[1, 0], [0, 1]]), np.array([[-1, 1], [1, -1]])   # X <-> Y
+    tr = dict(t_obs=np.array([1.0, 2.0]), y=np.full((2, 1), 2e5), t0=0.0,
+              x0=np.array([4000, 0], np.int32), x0_hi=np.array([400000, 0], np.int32))
+    from paper_1606_08281_amd import lik
+    net = lik.Network(orders, stoich)
+
+    def run():
+        return lik.eval_batch(net, lik.OBS_GAUSSIAN, [0], 1e5, np.array([[1.0, 1.0]]), [tr], 4096,
+                              7, kernel=lik.KERNEL_GENERIC)
+    _say("interval longer than the stall limit: without the limit")
+    want = run()
+    t = time.perf_counter()
+    run()
+    limit_us = int((time.perf_counter() - t) * 1e6 / 4)     # half an interval
+    monkeypatch.setenv("LIK_FLOW_STALL_US", str(limit_us))
+    _say("interval longer than the stall limit of", limit_us, "us")
+    got = run()
+    assert got["status"][0] == 0 and np.array_equal(got["loglik"], want["loglik"])
