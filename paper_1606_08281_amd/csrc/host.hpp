@@ -38,7 +38,7 @@ struct lik_network {
         hipFunction_t flow = nullptr;        // lik_flow_spec
     };
     std::map<std::pair<int, int>, SpecKernels> spec;
-    std::string spec_path[2];  // their files in the disk cache, per precision (once formed)
+    std::string spec_file[2];  // their files in the disk cache, per precision (once formed)
     // captured launch sequences of lik_eval_batch_device (LIK_FLAG_GRAPH)
     struct Graph {
         hipGraph_t graph = nullptr;

@@ -246,8 +246,8 @@ std::string specialized_source(const lik_network &net, int precision) {
 
 namespace {
 
-// The disk cache's file for a generated source.
-std::string cache_path(const std::string &src) {
+// The name of a generated source's file in the disk cache.
+std::string cache_file(const std::string &src) {
     // the key covers everything the code object depends on: the generated
     // source, the embedded kernel headers, the options and the compiler
     std::string key = src;
@@ -261,12 +261,12 @@ std::string cache_path(const std::string &src) {
     key += " hiprtc " + std::to_string(rtc_major) + "." + std::to_string(rtc_minor);
     char hex[32];
     snprintf(hex, sizeof(hex), "%016llx", (unsigned long long)fnv1a(key));
-    return cache_dir() + "/prop_" + hex + ".co";
+    return std::string("/prop_") + hex + ".co";
 }
 
 // Code object of a generated source: from the disk cache or compiled now.
 bool code_for_source(const std::string &src, std::vector<char> *code, std::string *err) {
-    const std::string dir = cache_dir(), path = cache_path(src);
+    const std::string dir = cache_dir(), path = dir + cache_file(src);
     if (read_file(path, code)) return true;
     if (!compile(src, code, err)) return false;
     write_file_atomic(dir, path, *code);
@@ -327,9 +327,9 @@ bool specialized_available(lik_network &net, int precision, bool may_load) {
     std::lock_guard<std::mutex> g(net.spec_lock);
     if (net.spec.count({dev, precision})) return true;
     if (!may_load) return false;
-    std::string &path = net.spec_path[precision == LIK_FP32_MIXED ? 1 : 0];
-    if (path.empty()) path = cache_path(specialized_source(net, precision));
-    return access(path.c_str(), R_OK) == 0;
+    std::string &file = net.spec_file[precision == LIK_FP32_MIXED ? 1 : 0];
+    if (file.empty()) file = cache_file(specialized_source(net, precision));
+    return access((cache_dir() + file).c_str(), R_OK) == 0;
 }
 
 namespace {
@@ -337,7 +337,7 @@ namespace {
 // the life of the process (a set of networks has no handle that owns them).
 std::mutex g_multi_mu;
 std::map<std::pair<int, std::string>, std::pair<hipModule_t, hipFunction_t>> g_multi;
-std::map<std::string, std::string> g_multi_path;  // source -> its file in the disk cache
+std::map<std::string, std::string> g_multi_file;  // source -> its file in the disk cache
 }  // namespace
 
 bool specialized_multi_available(const std::vector<lik_network *> &nets, int precision) {
@@ -346,10 +346,10 @@ bool specialized_multi_available(const std::vector<lik_network *> &nets, int pre
     const std::string src = specialized_multi_source(nets, precision);
     std::lock_guard<std::mutex> g(g_multi_mu);
     if (g_multi.count({dev, src})) return true;
-    if (g_multi_path.size() > 64) g_multi_path.clear();
-    std::string &path = g_multi_path[src];
-    if (path.empty()) path = cache_path(src);
-    return access(path.c_str(), R_OK) == 0;
+    if (g_multi_file.size() > 64) g_multi_file.clear();
+    std::string &file = g_multi_file[src];
+    if (file.empty()) file = cache_file(src);
+    return access((cache_dir() + file).c_str(), R_OK) == 0;
 }
 
 bool load_source(const std::string &src, hipModule_t *mod, std::string *err) {
@@ -362,7 +362,8 @@ bool load_source(const std::string &src, hipModule_t *mod, std::string *err) {
     (void)hipGetLastError();
     code.clear();
     if (!compile(src, &code, err)) return false;
-    write_file_atomic(cache_dir(), cache_path(src), code);
+    const std::string dir = cache_dir();
+    write_file_atomic(dir, dir + cache_file(src), code);
     const hipError_t e = hipModuleLoadData(mod, code.data());
     if (e == hipSuccess) return true;
     (void)hipGetLastError();

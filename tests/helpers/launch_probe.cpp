@@ -2,8 +2,10 @@
 // answered here (this program's definitions come before the runtime's), device
 // memory is host memory that no kernel touches, and every kernel launch is
 // printed as "name blocks threads stream".
-//   batch n_theta n_obs n_particles schedule
-//   requests n_theta n_obs n_particles schedule
+//   batch n_theta n_obs n_particles schedule [kernel cache...]
+//   requests n_theta n_obs n_particles schedule [kernel cache...]
+//     kernel: LIK_KERNEL_* (generic if not given); the call is made once per
+//     kernel cache folder, in this order
 //   groups n_groups failing: one engine iteration of n_groups groups beside
 //     each other, the launch of group `failing` (-1: none) refused; stream
 //     records and waits are printed as "record stream" and "wait stream stream"
@@ -58,6 +60,21 @@ hipError_t hipFree(void *p) { free(p); return hipSuccess; }
 hipError_t hipMemcpyAsync(void *, const void *, size_t, hipMemcpyKind, hipStream_t) { return hipSuccess; }
 hipError_t hipStreamCreate(hipStream_t *s) { *s = (hipStream_t)0x10; return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipModuleLoadData(hipModule_t *m, const void *) { *m = (hipModule_t)0x20; return hipSuccess; }
+hipError_t hipModuleUnload(hipModule_t) { return hipSuccess; }
+hipError_t hipModuleGetFunction(hipFunction_t *f, hipModule_t, const char *name) {
+    *f = (hipFunction_t)strdup(name);
+    return hipSuccess;
+}
+hipError_t hipModuleOccupancyMaxActiveBlocksPerMultiprocessor(int *n, hipFunction_t, int, size_t) {
+    *n = 24;
+    return hipSuccess;
+}
+hipError_t hipModuleLaunchKernel(hipFunction_t f, unsigned gx, unsigned, unsigned, unsigned bx,
+                                 unsigned, unsigned, unsigned, hipStream_t s, void **, void **) {
+    printf("%s %u %u %p\n", (const char *)f, gx, bx, (void *)s);
+    return hipSuccess;
+}
 hipError_t hipEventRecord(hipEvent_t e, hipStream_t s) {
     g_recorded[e] = s;
     printf("record %p\n", (void *)s);
@@ -117,8 +134,9 @@ static int iteration(int n, int failing) {
 int main(int argc, char **argv) {
     const std::string what = argc > 1 ? argv[1] : "";
     if (what == "groups" && argc == 4) return iteration(atoi(argv[2]), atoi(argv[3]));
-    if (argc != 6) return 2;
+    if (argc < 6 || argc == 7) return 2;
     const int n = atoi(argv[2]), T = atoi(argv[3]), H = atoi(argv[4]), schedule = atoi(argv[5]);
+    const int kernel = argc > 6 ? atoi(argv[6]) : LIK_KERNEL_GENERIC;
     const int32_t orders[2] = {0, 1}, stoich[2] = {1, -1};  // immigration and death
     lik_network_t net = nullptr;
     if (lik_create_network(1, 2, orders, stoich, &net) != LIK_OK) return 3;
@@ -138,22 +156,25 @@ int main(int argc, char **argv) {
     obs.n_observed = 1;
     obs.sigma = 1.0;
     int rc = LIK_OK;
-    if (what == "batch") {
-        const lik_eval_opts o = {LIK_FP64, LIK_KERNEL_GENERIC, 0, nullptr, 0, 0};
-        const size_t bytes = lik_workspace_size(net, n, 1, H);
-        void *ws = malloc(bytes);
-        rc = lik_eval_batch_device(net, &obs, &o, n, theta.data(), &data, offs, H, 1, ll.data(),
-                                   st.data(), nullptr, ws, bytes, nullptr);
-    } else {
-        lik_request r;
-        memset(&r, 0, sizeof(r));
-        r.net = net;
-        r.obs = obs;
-        r.n_theta = n;
-        r.theta = theta.data();
-        r.data = data;
-        r.n_particles = H;
-        rc = lik_eval_requests(&r, 1, &tu, LIK_KERNEL_GENERIC, ll.data(), st.data(), nullptr);
+    for (int call = argc > 6 ? 7 : 6; rc == LIK_OK && call < (argc > 6 ? argc : 7); ++call) {
+        if (argc > 6) setenv("LIK_KERNEL_CACHE", argv[call], 1);
+        if (what == "batch") {
+            const lik_eval_opts o = {LIK_FP64, kernel, 0, nullptr, 0, 0};
+            const size_t bytes = lik_workspace_size(net, n, 1, H);
+            void *ws = malloc(bytes);
+            rc = lik_eval_batch_device(net, &obs, &o, n, theta.data(), &data, offs, H, 1, ll.data(),
+                                       st.data(), nullptr, ws, bytes, nullptr);
+        } else {
+            lik_request r;
+            memset(&r, 0, sizeof(r));
+            r.net = net;
+            r.obs = obs;
+            r.n_theta = n;
+            r.theta = theta.data();
+            r.data = data;
+            r.n_particles = H;
+            rc = lik_eval_requests(&r, 1, &tu, kernel, ll.data(), st.data(), nullptr);
+        }
     }
     if (rc != LIK_OK) printf("error %d %s\n", rc, lik_last_error());
     return rc == LIK_OK ? 0 : 1;

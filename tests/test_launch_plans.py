@@ -103,3 +103,29 @@ def test_ordering_sums_are_cleared_before_the_admission(launches, entry, admit):
     assert names.count("k_order_reset") == 1
     assert names.index("k_order_reset") < names.index(admit) < names.index("k_order_count")
     assert "k_order_reset" not in [r[0] for r in launches(entry, 4, 3, 64, 1)]
+
+
+@pytest.mark.parametrize("entry,generic,cached", [("batch", "k_flow", "lik_flow_spec"),
+                                                  ("requests", "k_flow_multi",
+                                                   "lik_flow_spec_multi")])
+def test_automatic_choice_takes_the_cached_kernel(launches, entry, generic, cached, monkeypatch,
+                                                  tmp_path):
+    """A batch too small to pay for a compile: the specialised kernel where the
+    disk cache of the moment of the call holds it, else the generic one, and
+    nothing is compiled."""
+    full, empty = tmp_path / "full", tmp_path / "empty"
+    empty.mkdir()
+    monkeypatch.setenv("LIK_KERNEL_CACHE", str(full))
+    net = lik.Network(np.array([[0], [1]]), np.array([[1], [-1]]))   # the probe's network
+    net.precompile()
+    lik.precompile_requests([net], lik.FP64)
+
+    def kernels(kernel, *folders):
+        return [r[0] for r in launches(entry, 4, 3, 64, 1, kernel, *folders)
+                if r[0] in (generic, cached)]
+    assert kernels(lik.KERNEL_AUTO, empty) == [generic]
+    assert kernels(lik.KERNEL_AUTO, full) == [cached]
+    assert kernels(lik.KERNEL_AUTO, empty, full) == [generic, cached]
+    assert kernels(lik.KERNEL_GENERIC, full) == [generic]
+    assert kernels(lik.KERNEL_AUTO, full, empty) == [cached, cached]   # loaded by then
+    assert not list(empty.iterdir())
