@@ -608,8 +608,8 @@ typedef struct lik_ode_data {
  * constant indices, cached on disk like the networks' kernels; LIK_EDEVICE if
  * that fails) or LIK_KERNEL_AUTO (specialised, else generic); every variant
  * gives identical results.  Each (theta, trajectory) pair is integrated by
- * one GPU lane (up to 49,152 pairs, specialised: by a group of 16 or 32); the
- * lanes take pairs from a shared counter, the trajectories with the most
+ * one GPU lane, or (specialised, small populations of models large enough to
+ * gain by it) by a group of 16 or 32; the lanes take pairs from a shared counter, the trajectories with the most
  * stops (observations plus input breakpoints) first, which changes only the
  * speed.  Synchronous; allocates its device memory.
  */

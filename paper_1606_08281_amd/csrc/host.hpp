@@ -89,6 +89,10 @@ bool precompile_multi(const std::vector<lik_network *> &nets, int precision, std
 bool load_source(const std::string &src, hipModule_t *mod, std::string *err);
 bool precompile_source(const std::string &src, std::string *err);
 
+// (theta, trajectory) pairs up to which a deterministic model's specialised
+// kernel gives each a group of lanes, on a GPU of `cus` compute units (0: never).
+size_t ode_group_pairs(const lik_ode_model &m, uint32_t cus);
+
 // Compile (or find in the disk cache) without loading: needs no device.
 bool precompile_specialized(const lik_network &net, int precision, std::string *err);
 

@@ -18,8 +18,10 @@
 #include <stdio.h>
 
 #include <algorithm>
+#include <array>
 #include <map>
 #include <mutex>
+#include <set>
 #include <sstream>
 #include <string>
 #include <vector>
@@ -37,6 +39,8 @@ struct lik_ode_t_ {
         hipModule_t mod = nullptr;
         hipFunction_t fn = nullptr;     // lik_ode_spec: one lane per pair
         hipFunction_t group = nullptr;  // lik_ode_group: 16 or 32 lanes per pair, or null
+        size_t group_pairs = 0;         // pairs up to which it is the faster one
+        unsigned group_lanes = 0, group_lds = 0;
     };
     std::map<int, Spec> spec;
     // the terms and x0_param in device memory, per device (made on first use)
@@ -99,19 +103,87 @@ int ode_par_stride(int V) { return V % 2 == 1 || V == LIK_ODE_MAX_PARAMS ? V : V
 // LDS bytes of the specialised kernel's launch: one parameter slot per lane.
 size_t ode_par_lds(int V) { return (size_t)64 * ode_par_stride(V) * sizeof(double); }
 
-// Lanes per pair of the group kernel: 16 up to 16 species, else 32; 0 (no such
-// kernel) where the terms would take more than four rounds of them.
-int ode_group_lanes(const lik_ode_model &m) {
-    const int L = m.n_species <= 16 ? 16 : 32;
-    return m.n_terms <= 4 * L ? L : 0;
+// The group kernel's layout of a model: lanes per pair (16 up to 16 species,
+// else 32), rounds of them over the terms, each species' terms in term order
+// (k + 1 entering, -(k + 1) leaving) and where a round's factor slot divides.
+struct OdeShape {
+    int lanes = 0, rounds = 0;
+    std::vector<std::vector<int>> list;
+    size_t most = 1;                    // longest of the lists
+    std::vector<std::array<bool, 3>> div;
+    int slots = 0;                      // dividing (round, slot) places
+    int quotients = 0;                  // different dividing factors of the model
+};
+
+// an input factor reads no species; a species factor no parameter
+bool reads_species(const lik_ode_term &t, int f) { return t.kind[f] != LIK_ODE_INPUT; }
+bool divides(const lik_ode_term &t, int f) {
+    return reads_species(t, f) && t.kind[f] != LIK_ODE_SPECIES;
 }
-int ode_group_rounds(const lik_ode_model &m) {
-    const int L = ode_group_lanes(m);
-    return (m.n_terms + L - 1) / L;
+
+OdeShape ode_shape(const lik_ode_model &m) {
+    OdeShape s;
+    const int NT = m.n_terms;
+    s.lanes = m.n_species <= 16 ? 16 : 32;
+    s.rounds = (NT + s.lanes - 1) / s.lanes;
+    s.list.resize((size_t)m.n_species);
+    s.div.assign((size_t)s.rounds, {false, false, false});
+    std::set<std::array<int, 3>> quotients;
+    for (int k = 0; k < NT; ++k) {
+        const lik_ode_term &T = m.terms[k];
+        if (T.from >= 0) s.list[(size_t)T.from].push_back(-(k + 1));
+        if (T.to >= 0) s.list[(size_t)T.to].push_back(k + 1);
+        for (int f = 0; f < T.n_factors; ++f)
+            if (divides(T, f)) {
+                quotients.insert({T.kind[f], T.species[f], T.param[f]});
+                bool &place = s.div[(size_t)(k / s.lanes)][(size_t)f];
+                s.slots += place ? 0 : 1;
+                place = true;
+            }
+    }
+    for (const auto &l : s.list) s.most = std::max(s.most, l.size());
+    s.quotients = (int)quotients.size();
+    return s;
 }
-size_t ode_group_lds(const lik_ode_model &m) {
-    const int L = ode_group_lanes(m);
-    return (size_t)(64 / L) * (L + ode_group_rounds(m) * L + m.n_params) * sizeof(double);
+
+}  // namespace
+
+// Pairs up to which a group of lanes per pair is the faster form on a GPU of
+// `cus` compute units (0: never, and the kernel is not built).  In microseconds
+// per step attempt, fitted to 25 models of 1 to 32 species and 2 to 101 terms:
+// one lane per pair runs every species and term in turn (wide); a group runs its
+// longest list and its dividing rounds (group), where a wavefront of pairs is
+// alone on its SIMD, and takes `busy` of the SIMD's time where many share it.
+// The wide form is held up by its slowest pair, the shared one by the mean:
+// slowest / mean was 2 for linear models, 3 to 7 where most factors saturate.
+//   lanes per pair     wide / group at 1,000 pairs   at 16,000     at 49,000
+//   1 species          0.095 / 0.112 ms              0.109 / 0.292  0.211 / 0.658
+//   8, linear          0.213 / 0.162                 0.242 / 0.344  0.357 / 0.708
+//   8, saturating      0.321 / 0.191                 0.466 / 0.360  0.731 / 0.688
+//   8, 61 terms on one 39.5 / 225                    65.0 / 375     96.8 / 614
+//   14, ERK            10.9 / 4.65                   12.6 / 5.81    13.3 / 11.8
+//   17, 52 terms       1.20 / 0.594                  1.32 / 1.28    1.74 / 2.74
+//   32, linear         0.991 / 0.171                 1.01 / 0.369   1.33 / 0.779
+// On 22 random models of 2 to 28 species at 500 to 45,000 pairs the choice was
+// 1.5 % from the faster form on average, at worst 1.19 times the one-lane form.
+size_t lik::ode_group_pairs(const lik_ode_model &m, uint32_t cus) {
+    const OdeShape s = ode_shape(m);
+    if (s.rounds > 4) return 0;
+    const double list = (double)s.most, slots = s.slots;
+    const double group = 0.7 + 0.4 * list + 0.35 * slots;
+    const double wide = 0.25 + 0.25 * m.n_species + 0.04 * m.n_terms + 0.2 * s.quotients;
+    if (group >= wide) return 0;
+    const double busy = (1.2 + 0.15 * list + 0.2 * slots) * (s.lanes == 32 ? 0.7 : 1.0);
+    const double slowest = 2.0 + 3.0 * s.quotients / m.n_terms;
+    const double per_simd = sqrt(wide * wide - group * group) * slowest / busy;
+    // up to three lanes of four: beyond, lanes of the wide form take further pairs
+    return (size_t)(std::min(per_simd * 64.0 / s.lanes, 48.0) * 4.0 * cus);
+}
+
+namespace {
+
+size_t ode_group_lds(const lik_ode_model &m, const OdeShape &s) {
+    return (size_t)(64 / s.lanes) * (s.lanes + s.rounds * s.lanes + m.n_params) * sizeof(double);
 }
 
 // The FRET ratio or observed species as an expression over pv and x.
@@ -129,7 +201,9 @@ void emit_obs(std::ostringstream &o, const lik_ode_model &m) {
 
 // The tables of ode_run_group's model (struct OdeGroup).
 void emit_group_model(std::ostringstream &o, const lik_ode_model &m) {
-    const int L = ode_group_lanes(m), R = ode_group_rounds(m), U = m.n_species, NT = m.n_terms;
+    const OdeShape shape = ode_shape(m);
+    const int U = m.n_species, NT = m.n_terms;
+    const size_t most = shape.most;
     auto row = [&](const char *type, const char *name, auto &&value) {
         o << "  static constexpr " << type << " " << name << "[" << NT << "] = {";
         for (int k = 0; k < NT; ++k) o << (k ? "," : "") << value(k);
@@ -140,47 +214,32 @@ void emit_group_model(std::ostringstream &o, const lik_ode_model &m) {
         for (int k = 0; k < NT; ++k) {
             o << (k ? "," : "") << "{";
             for (int f = 0; f < 3; ++f)
-                o << (f ? "," : "") << (f < m.terms[k].n_factors ? value(k, f) : 0);
+                o << (f ? "," : "") << (f < m.terms[k].n_factors ? value(m.terms[k], f) : 0);
             o << "}";
         }
         o << "};\n";
     };
-    std::vector<std::vector<int>> list((size_t)U);
-    for (int k = 0; k < NT; ++k) {
-        if (m.terms[k].from >= 0) list[(size_t)m.terms[k].from].push_back(-(k + 1));
-        if (m.terms[k].to >= 0) list[(size_t)m.terms[k].to].push_back(k + 1);
-    }
-    size_t most = 1;
-    for (auto &v : list) most = std::max(most, v.size());
     o << "struct OdeGroup {\n  static constexpr int U = " << U << ", NT = " << NT << ", V = "
-      << m.n_params << ", L = " << L << ", ROUNDS = " << R << ", MAXL = " << most << ";\n";
+      << m.n_params << ", L = " << shape.lanes << ", ROUNDS = " << shape.rounds << ", MAXL = "
+      << most << ";\n";
     row("int", "nf", [&](int k) { return m.terms[k].n_factors; });
     row("int", "rate_param", [&](int k) { return m.terms[k].rate_param; });
     row("double", "scale", [&](int k) { return hexd(m.terms[k].rate_scale); });
-    // an input factor reads no species and no parameter
-    auto reads = [&](int k, int f) { return m.terms[k].kind[f] != LIK_ODE_INPUT; };
-    auto divides = [&](int k, int f) {
-        return reads(k, f) && m.terms[k].kind[f] != LIK_ODE_SPECIES;
-    };
-    row3("kind", [&](int k, int f) { return m.terms[k].kind[f]; });
-    row3("sp", [&](int k, int f) { return reads(k, f) ? m.terms[k].species[f] : 0; });
-    row3("par", [&](int k, int f) { return divides(k, f) ? m.terms[k].param[f] : 0; });
-    o << "  static constexpr bool DIV[" << R << "][3] = {";
-    for (int r = 0; r < R; ++r) {
+    row3("kind", [](const lik_ode_term &t, int f) { return t.kind[f]; });
+    row3("sp", [](const lik_ode_term &t, int f) { return reads_species(t, f) ? t.species[f] : 0; });
+    row3("par", [](const lik_ode_term &t, int f) { return divides(t, f) ? t.param[f] : 0; });
+    o << "  static constexpr bool DIV[" << shape.rounds << "][3] = {";
+    for (int r = 0; r < shape.rounds; ++r) {
         o << (r ? "," : "") << "{";
-        for (int f = 0; f < 3; ++f) {
-            bool any = false;
-            for (int k = r * L; k < std::min(NT, (r + 1) * L); ++k)
-                any = any || (f < m.terms[k].n_factors && divides(k, f));
-            o << (f ? "," : "") << (any ? "true" : "false");
-        }
+        for (size_t f = 0; f < 3; ++f)
+            o << (f ? "," : "") << (shape.div[(size_t)r][f] ? "true" : "false");
         o << "}";
     }
     o << "};\n  static constexpr int list[" << U << "][" << most << "] = {";
     for (int u = 0; u < U; ++u) {
+        const std::vector<int> &l = shape.list[(size_t)u];
         o << (u ? "," : "") << "{";
-        for (size_t i = 0; i < most; ++i)
-            o << (i ? "," : "") << (i < list[(size_t)u].size() ? list[(size_t)u][i] : 0);
+        for (size_t i = 0; i < most; ++i) o << (i ? "," : "") << (i < l.size() ? l[i] : 0);
         o << "}";
     }
     o << "};\n  __device__ static double obs(const double *pv, const double *x) {\n    (void)pv;\n";
@@ -247,11 +306,12 @@ std::string ode_spec_source(const lik_ode_model &m) {
          "    const double *pv = row(p);\n    (void)pv;\n";
     emit_obs(o, m);
     o << "  }\n};\n";
-    if (ode_group_lanes(m)) emit_group_model(o, m);
+    const bool group = ode_group_pairs(m, 1) > 0;
+    if (group) emit_group_model(o, m);
     o << "}  // namespace lik\n"
          "extern \"C\" __global__ void __launch_bounds__(64) lik_ode_spec(lik::OdeArgs a) {\n"
          "  lik::ode_run<lik::OdeSpec>(a);\n}\n";
-    if (ode_group_lanes(m))
+    if (group)
         o << "extern \"C\" __global__ void __launch_bounds__(64) lik_ode_group(lik::OdeArgs a) {\n"
              "  lik::ode_run_group<lik::OdeGroup>(a, lik_ode_par);\n}\n";
     return o.str();
@@ -271,8 +331,13 @@ lik_ode_t_::Spec ode_spec_kernel(lik_ode_t_ &md, std::string *err) {
     lik_ode_t_::Spec s;
     if (!load_source(ode_spec_source(md.m), &s.mod, err)) return {};
     hipError_t e = hipModuleGetFunction(&s.fn, s.mod, "lik_ode_spec");
-    if (e == hipSuccess && ode_group_lanes(md.m))
+    if (e == hipSuccess && ode_group_pairs(md.m, 1) > 0) {
+        const OdeShape shape = ode_shape(md.m);
+        s.group_pairs = ode_group_pairs(md.m, compute_units());
+        s.group_lanes = (unsigned)shape.lanes;
+        s.group_lds = (unsigned)ode_group_lds(md.m, shape);
         e = hipModuleGetFunction(&s.group, s.mod, "lik_ode_group");
+    }
     if (e != hipSuccess) {
         *err = std::string("hipModuleGetFunction: ") + hipGetErrorString(e);
         (void)hipModuleUnload(s.mod);
@@ -406,13 +471,6 @@ struct OdeLaunch {
     unsigned pairs = 64;           // (theta, trajectory) pairs per workgroup
 };
 
-// Up to this many pairs the group kernel is used: with one lane per pair they
-// leave SIMDs without a wavefront (65,536 lanes fill each with one).  ERK
-// batches, one lane per pair / groups of 16: 200 rate vectors (1,200 pairs)
-// 12.1 / 4.6 ms, 2,730 (16,380) 13.1 / 6.7 ms; from there the groups' time
-// grows by 0.22 ms per 1,000 pairs, the other's stays near 15 ms up to 50,000.
-constexpr size_t kOdeGroupPairs = 49152;
-
 int pick_kernel(lik_ode_t_ &md, int32_t kernel, size_t F, OdeLaunch *out) {
     *out = OdeLaunch{};
     if (kernel == LIK_KERNEL_GENERIC) return LIK_OK;
@@ -421,10 +479,10 @@ int pick_kernel(lik_ode_t_ &md, int32_t kernel, size_t F, OdeLaunch *out) {
     if (!s.fn && kernel == LIK_KERNEL_SPECIALIZED)
         return fail(LIK_EDEVICE, "specialised ODE kernel unavailable: " + msg);
     if (!s.fn) return LIK_OK;
-    if (s.group && F <= kOdeGroupPairs) {
+    if (s.group && F <= s.group_pairs) {
         out->spec = s.group;
-        out->lds = (unsigned)ode_group_lds(md.m);
-        out->pairs = (unsigned)(64 / ode_group_lanes(md.m));
+        out->lds = s.group_lds;
+        out->pairs = 64 / s.group_lanes;
     } else {
         out->spec = s.fn;
         out->lds = (unsigned)ode_par_lds(md.m.n_params);

@@ -419,7 +419,8 @@ __device__ __forceinline__ void ode_run(const OdeArgs &a) {
 // the same bit for bit.  A 200-vector batch of the 14-species ERK model took
 // 12.1 ms with one lane per pair and takes 4.6 ms with 16; a pair costs about
 // three times the issue slots, so the launch takes this form only where the
-// other would leave SIMDs without a wavefront (kOdeGroupPairs).
+// other would leave SIMDs without a wavefront, and only for models whose lists
+// are short (ode_group_pairs).
 //
 // Model: U, NT (terms), V (parameters), L, ROUNDS (terms per lane), MAXL (most
 // terms of a species), and the tables

@@ -129,3 +129,59 @@ def test_automatic_choice_takes_the_cached_kernel(launches, entry, generic, cach
     assert kernels(lik.KERNEL_GENERIC, full) == [generic]
     assert kernels(lik.KERNEL_AUTO, full, empty) == [cached, cached]   # loaded by then
     assert not list(empty.iterdir())
+
+
+SPECIES, SATURATING = 0, 1
+
+
+def _chain(U, per, kinds):
+    """U species in a chain, `per` terms out of each."""
+    terms = [{"to": 0}]
+    for s in range(U):
+        for q in range(per):
+            to = {"to": s + 1 + q} if s + 1 < U and s + 1 + q < U else {}
+            terms.append(dict(frm=s, factors=[(kinds[(s + q) % len(kinds)], s, 3)], **to))
+    return U, terms
+
+
+def _hub(U, n):
+    """n terms out of and into one species."""
+    return U, [dict(frm=0, factors=[(SATURATING if k % 3 == 0 else SPECIES, k % U, 3)])
+               for k in range(n)]
+
+
+def _group_pairs(U, terms, cus=256):
+    import ctypes
+    arr = (lik.OdeTerm * len(terms))()
+    for T, t in zip(arr, terms):
+        T.frm, T.to, T.rate_param = t.get("frm", -1), t.get("to", -1), -1
+        T.n_factors = len(t.get("factors", []))
+        for j, factor in enumerate(t.get("factors", [])):
+            T.kind[j], T.species[j], T.param[j] = factor
+    m = lik.OdeModelC(U, 4, len(terms), ctypes.addressof(arr), None, 0, 0, 0, -1, 1.0,
+                      (ctypes.c_int32 * 5)())
+    f = getattr(lik.lib(), "_ZN3lik15ode_group_pairsERK13lik_ode_modelj")   # lik::ode_group_pairs
+    f.restype, f.argtypes = ctypes.c_size_t, [ctypes.c_void_p, ctypes.c_uint32]
+    return f(ctypes.byref(m), cus)
+
+
+def test_deterministic_models_take_the_form_that_measured_faster():
+    """Pairs up to which a group of lanes integrates one: none where the one-lane
+    form was faster at 1,000 pairs already, and between the sizes that were
+    measured on either side of the crossing elsewhere."""
+    from paper_1606_08281_amd import workloads as W
+    never = [_chain(1, 1, [SPECIES]), _chain(1, 1, [SATURATING]), _chain(2, 1, [SPECIES]),
+             _chain(2, 3, [SATURATING, SPECIES]), _chain(4, 1, [SPECIES]),
+             _chain(4, 15, [SATURATING, SPECIES]), _hub(8, 60), _hub(32, 100)]
+    for U, terms in never:
+        assert _group_pairs(U, terms) == 0, (U, len(terms))
+    for (U, terms), above, below in [(_chain(8, 1, [SPECIES]), 4000, 16000),
+                                     (_chain(8, 1, [SATURATING]), 32000, 49153),
+                                     (_chain(16, 1, [SPECIES]), 16000, 32000),
+                                     (_chain(17, 1, [SPECIES]), 16000, 32000),
+                                     (_chain(32, 1, [SATURATING]), 49000, 49153)]:
+        assert above <= _group_pairs(U, terms) < below, (U, len(terms))
+    erk = W.erk_model()
+    assert _group_pairs(erk["U"], erk["terms"]) == 49152
+    assert _group_pairs(erk["U"], erk["terms"], cus=128) == 24576
+    assert _group_pairs(8, _chain(8, 9, [SPECIES])[1][:65]) == 0     # more than four rounds of 16
