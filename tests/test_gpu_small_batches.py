@@ -147,3 +147,74 @@ def test_long_interval_is_no_stall(monkeypatch):
     _say("interval longer than the stall limit of", limit_us, "us")
     got = run()
     assert got["status"][0] == 0 and np.array_equal(got["loglik"], want["loglik"])
+
+
+def _three_species_workload():
+    """26 reactions of 3 species: births, deaths, conversions and pairs, each
+    several times (few species: pools of up to 6 groups fit)."""
+    kinds = [({}, {0: 1}, 20.0), ({}, {1: 1}, 10.0), ({0: 1}, {0: -1}, 0.3),
+             ({1: 1}, {1: -1, 2: 1}, 0.3), ({2: 1}, {2: -1}, 0.3), ({2: 1}, {2: -1, 0: 1}, 0.2),
+             ({0: 1, 1: 1}, {0: -1}, 0.002), ({1: 2}, {1: -2, 2: 1}, 0.002)]
+    orders, stoich = np.zeros((26, 3), np.int32), np.zeros((26, 3), np.int32)
+    rates = np.zeros(26)
+    for r in range(26):
+        p, v, rates[r] = kinds[r % len(kinds)]
+        for u, k in p.items():
+            orders[r, u] = k
+        for u, k in v.items():
+            stoich[r, u] = k
+    rng = np.random.default_rng(2)
+    t = np.array([1.0, 2.0, 3.0])
+    tr = {"t_obs": t, "y": rng.normal(60.0, 10.0, (3, 1)), "t0": 0.0,
+          "x0": np.array([40, 30, 50], np.int32)}
+    theta = rates * np.exp(rng.normal(0.0, 0.3, (512, 26)))
+    net = W.Network("3x26", ["A", "B", "C"], orders, stoich)
+    return W.Workload("3x26", net, 0, [0], 10.0, theta, [tr], 200)
+
+
+@pytest.mark.parametrize("precision", [0, 1])
+@pytest.mark.parametrize("network", ["20x40", "3x26"])
+def test_event_cap_in_the_branch_free_main_loop(orc, network, precision):
+    """More than 24 reactions, whole groups of 64 (too many of them to be split);
+    3 species: pools whose lanes take further particles.  The cap before, on and
+    after the second event of a random block in FP32-mixed."""
+    if network == "3x26":
+        wl, caps = _three_species_workload(), (1, 281, 310, 311, 330, 331, 345, 400)
+    else:
+        wl = W.random_network_workload(n_theta=512, n_particles=200, n_obs=3)
+        caps = (1, 301, 600, 601, 700, 701, 801, 1000)
+    idx = np.arange(5, 512, 73)
+    capped = 0
+    for cap in caps:
+        ref = _oracle(orc, wl, theta=wl.theta[idx], theta_ids=idx, precision=precision,
+                      event_cap=cap)
+        capped += int((ref["status"] == 1).sum())
+        for kernel, pool_min in ((1, 1), (2, 1), (2, 4)):
+            _say(network, "cap", cap, "precision", precision, "kernel", kernel, "pool", pool_min)
+            got = _gpu(wl, precision=precision, kernel=kernel, event_cap=cap,
+                       tuning={"schedule": 0, "pool_min": pool_min, "pool_max": 6,
+                               "items_per_cu": 0})
+            assert np.array_equal(got["status"][idx], ref["status"])
+            assert np.array_equal(np.isnan(got["loglik"][idx]), np.isnan(ref["loglik"]))
+            ok = ref["status"] == 0
+            assert np.array_equal(got["filter_events"][idx][ok], ref["events"][ok])
+            assert np.array_equal(got["final_state"][idx][ok], ref["final_state"][ok])
+    assert 0 < capped < len(caps) * len(idx)
+
+
+@pytest.mark.parametrize("kernel", [1, 2])
+def test_split_filters_that_wait(kernel):
+    """Hundreds of filters with uneven chains under a short queue: filters are
+    split while others are parked, and more would be split than the launch has
+    wavefronts or ring room for.  The per-interval schedule's results."""
+    rng = np.random.default_rng(11)
+    wl = W.immigration_death_workload(1, t_obs=5.0 * np.arange(1, 9))
+    for H, n in ((150, 350), (64, 1500), (1000, 40)):
+        theta = np.exp(rng.normal([3.0, -2.0], [1.0, 0.3], (n, 2)))
+        want = _gpu(wl, theta=theta, H=H, kernel=kernel, tuning={"schedule": 0})
+        for urgent in (0, 1 << 30):
+            _say("split and parked filters H", H, "filters", n, "urgent", urgent)
+            got = _gpu(wl, theta=theta, H=H, kernel=kernel,
+                       tuning={"schedule": 1, "backlog_per_cu": 1, "urgent_events": urgent})
+            for k in ("loglik", "status", "filter_events", "final_state"):
+                assert np.array_equal(got[k], want[k], equal_nan=True), k
