@@ -136,8 +136,12 @@ typedef struct lik_tuning {
     uint32_t pool_events;  /* target events per lane per work item */
     int32_t pool_first;    /* >= 1, <= 64 */
     int32_t refill_min;    /* idle lanes of a wavefront that trigger a refill, 1..64 */
-    int32_t priority;      /* 1: raise the wavefront priority of the filters whose
-                              particles are expected to need the most events; 0: off */
+    int32_t priority;      /* schedule 0 and the server: 1: raise the wavefront priority of
+                              the filters whose particles are expected to need the most
+                              events; 0: off.  Schedule 1 ranks its wavefronts by itself,
+                              whatever is set here: those of the longest chains of
+                              intervals left issue first on a SIMD they share (256 Lac-Gfp
+                              rate vectors: 565 ms, 635 without) */
     int32_t items_per_cu;  /* pools grow only while an iteration keeps at least this
                               many work items per compute unit (>= 0; 0: always) */
     int32_t persistent;    /* 1: networks of at most 16 reactions run a persistent
@@ -609,9 +613,10 @@ typedef struct lik_ode_data {
  * that fails) or LIK_KERNEL_AUTO (specialised, else generic); every variant
  * gives identical results.  Each (theta, trajectory) pair is integrated by
  * one GPU lane, or (specialised, small populations of models large enough to
- * gain by it) by a group of 16 or 32; the lanes take pairs from a shared counter, the trajectories with the most
- * stops (observations plus input breakpoints) first, which changes only the
- * speed.  Synchronous; allocates its device memory.
+ * gain by it) by a group of 16 or 32; the lanes take pairs from a shared
+ * counter, the trajectories with the most stops (observations plus input
+ * breakpoints) first, which changes only the speed.  Synchronous; allocates its
+ * device memory.
  */
 int lik_ode_eval(lik_ode_t model, int32_t n_theta, const double *theta,
                  const lik_ode_data *data, double rtol, double atol, int32_t max_steps,

@@ -44,7 +44,8 @@
 // waits for its stores (stores_done) and then makes the hand-off known with an
 // atomic operation; the taker acquires at agent scope.  No store of this
 // kernel stays dirty in an L2 while another XCD may write or read its address
-// (the weights' scratch included).  Releasing plain stores instead wrote the
+// (the weights' scratch included), so every store of it has to go through
+// store_global or an agent-scope atomic.  Releasing plain stores instead wrote the
 // XCD's whole L2 back, three times per item: 326 -> 322 ms for 1024 telegraph
 // rate vectors in FP64, 213 -> 166 ms for 512 in FP32-mixed without.
 #pragma once
@@ -354,8 +355,8 @@ __device__ __forceinline__ uint32_t points_below(uint64_t x, uint64_t rho, uint6
 // run over particles lane-strided, so every lane's loads are independent.
 // The one order-dependent sum, S = sum e_j, follows k_weigh's order: each
 // lane adds its particles j = lane + 64 k in increasing k, then one
-// butterfly over the lanes.  The slot's lw array holds l_j, then e_j.  Resampling is taken from the
-// particles' side: with
+// butterfly over the lanes.  The slot's lw array holds l_j, then e_j.
+// Resampling is taken from the particles' side: with
 // J(x) = #{j >= 0 : j Q + rho < x}, particle i is the ancestor of exactly
 // the j in [J(H C_i), J(H C_{i+1})) -- the same a_j = min{i : H C_{i+1} >
 // j Q + rho} as the search over j, found without dependent loads.  Every
@@ -607,14 +608,16 @@ __device__ __forceinline__ void flow_push(const EngineArgs &e, const FlowArgs &f
             fa, item_code(e, f, cost, fa.g_par, flow_goal(fa, w, sum, nchunk, critical != 0)), H,
             nchunk);
         // wavefront priority for the longest chains left (2 and 4 times the
-        // average): 256 Lac-Gfp rate vectors 655 -> 598 ms
+        // average; tuning.priority is the per-interval schedule's): 256 Lac-Gfp
+        // rate vectors 635 -> 565 ms (means of three seeds)
         const double chain = (double)w * (double)(fa.n_slots - (int)ctl_load(fa, kCtlFinished));
         prio = critical || chain >= 4.0 * (double)sum ? 3 : chain >= 2.0 * (double)sum ? 1 : 0;
     }
     code = __builtin_amdgcn_readfirstlane(code);
     const int n_items = code_items(code, H);
     const int park = __builtin_amdgcn_readfirstlane(
-        (int)(!critical && !flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) && item_backlog(fa) >= (int32_t)fa.backlog));
+        (int)(!critical && !flow_urgent(e, fa, f, cost, code < kSplitCode ? code + 1 : 1) &&
+              item_backlog(fa) >= (int32_t)fa.backlog));
     if (lane == 0) {
         store_global(e.cost, (uint32_t)f, cost);
         store_global(e.pool, (uint32_t)f, (uint8_t)((prio << 6) | code));

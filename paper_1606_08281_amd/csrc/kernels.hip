@@ -33,12 +33,6 @@
 
 namespace lik {
 
-// ---------------------------------------------------------------------------
-// admit: fill the slots of one request.  Rates that are negative, infinite or
-// NaN -- and, for the binary32 step, beyond the binary32 range (they would
-// round to infinity, and infinity times a zero mass-action factor is NaN) --
-// mark every slot of that theta BAD_THETA before any simulation.
-// ---------------------------------------------------------------------------
 // An estimate of a slot's events per particle into the sum of the iteration of
 // parity p (only where iterations split by it).
 __device__ __forceinline__ uint64_t *order_sum(const EngineArgs &e, int p) {
@@ -49,6 +43,12 @@ __device__ __forceinline__ void add_order_sum(const EngineArgs &e, int p, uint32
         atomicAdd(reinterpret_cast<unsigned long long *>(order_sum(e, p)), (unsigned long long)per);
 }
 
+// ---------------------------------------------------------------------------
+// admit: fill the slots of one request.  Rates that are negative, infinite or
+// NaN -- and, for the binary32 step, beyond the binary32 range (they would
+// round to infinity, and infinity times a zero mass-action factor is NaN) --
+// mark every slot of that theta BAD_THETA before any simulation.
+// ---------------------------------------------------------------------------
 // Filter k of request r (theta k / M against trajectory k % M) into its slot.
 __device__ __forceinline__ void admit_one(FilterDesc *desc, const EngineArgs &e,
                                           const RequestArgs &r, int k) {

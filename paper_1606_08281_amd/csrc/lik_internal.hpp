@@ -163,7 +163,9 @@ struct EngineArgs {
 
 // Flow engine (one launch runs every interval of a batch; flow.hpp).  Ring
 // kRingItems holds work items, ring kRingParked the ids of filters whose
-// items wait for room.  Control words sit 128 bytes apart in ctl.
+// items wait for room.  Control words sit 128 bytes apart in ctl, except those
+// that only hand-offs of whole intervals touch, one after another: from
+// kCtlSeedItems on they share a line.
 constexpr int kFlowRings = 2;
 enum : int { kRingItems = 0, kRingParked = 1 };
 enum : int {

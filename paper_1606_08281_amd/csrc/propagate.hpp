@@ -364,8 +364,8 @@ __device__ __forceinline__ bool event_masked(const NetT &net, const Real *c, int
 // k_weigh).
 //
 // A work item is a pool of G * 64 consecutive particles of one filter (G set
-// per filter by k_order), or where the GPU would stand idle a part of 64.  Each lane runs one event per loop iteration; a lane
-// whose particle has reached the observation time finishes it and takes the
+// per filter by k_order), or where the GPU would stand idle a part of 64.  Each
+// lane runs one event per loop iteration; a lane whose particle has reached the observation time finishes it and takes the
 // next particle of the pool (ballot + rank among the idle lanes), so lanes are
 // not held up by the slowest particle of a fixed group of 64.  Which lane runs
 // a particle never changes its arithmetic or its random stream.
@@ -602,11 +602,17 @@ __device__ __forceinline__ void run_item(const EngineArgs &e, const NetT &net, u
         __builtin_amdgcn_s_setprio(1);
     }
     // (an item of at most 32 particles goes to the drain at once)
-    // A network of more than kBranchMax reactions leaves two wavefronts on a
-    // SIMD, where the branches of ssa_event cost more than they skip: 512 rate
-    // vectors of the 20 x 40 network 846 -> 803 ms with event_masked.  Six
-    // wavefronts hide them (telegraph: 323 ms, 335 with event_masked; Lac-Gfp,
-    // 18 reactions, 570 and 574).
+    // A kernel for more than kBranchMax reactions (RMAX: the network's own where
+    // it is specialised, 64 for every network the generic kernels of 8 species and
+    // 16 reactions do not take) leaves two wavefronts on a SIMD, where the branches
+    // of ssa_event cost more than they skip: 512 rate vectors of the 20 x 40
+    // network 846 -> 803 ms with event_masked.  Six wavefronts hide them
+    // (telegraph: 323 ms, 335 with event_masked; Lac-Gfp, 18 reactions, 570 and
+    // 574).  384 rate vectors of random networks, branches / event_masked, FP64 and
+    // FP32-mixed: specialised 6 x 26 5.50 / 5.30 and 5.04 / 4.07 ms, 10 x 30 7.51 /
+    // 7.56 and 5.45 / 5.10, 32 x 64 28.4 / 26.9 and 24.3 / 18.2; generic 9 x 5 8.7 /
+    // 8.5 and 10.4 / 9.4, 10 x 30 275 / 270 and 285 / 292, 32 x 64 1234 / 1225 and
+    // 1283 / 1298.
     constexpr int kBranchMax = 24;
     double lim = have ? t_end : -__builtin_inf();
     while (p1 - p0 > kPropBlock / 2) {

@@ -123,7 +123,8 @@ int lik_eval_requests(const lik_request *reqs, int32_t n_req, const lik_tuning *
     const size_t o_tcur = c.take((size_t)F * 4), o_fst = c.take((size_t)F * 4);
     const size_t o_ffl = c.take((size_t)F * 4), o_cost = c.take((size_t)F * 4);
     const size_t o_pool = c.take((size_t)F), o_fll = c.take((size_t)F * 8);
-    const size_t o_fev = c.take((size_t)F * 8), o_items = c.take(((size_t)chunks + kMaxGroups * split_waves()) * 4);
+    const size_t o_fev = c.take((size_t)F * 8), o_items =
+        c.take(((size_t)chunks + nets.size() * split_waves()) * 4);
     const size_t o_icount = c.take(kMaxGroups * 4), o_icur = c.take(kMaxGroups * 4);
     const size_t o_ocount = c.take(kMaxGroups * kCostKeys * 4);
     const size_t o_opos = c.take(kMaxGroups * kCostKeys * 4);
